@@ -14,8 +14,11 @@ OBJ = os.path.join(PKG, "_build")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libofmi.so")
 
-SOURCES = ["pyramid.hip", "lk_iter.hip", "lk_iter_u8.hip", "lk_iter_f32.hip", "lk_iter_f16.hip",
-           "runtime.hip", "batch.hip", "serve.hip", "extras.hip"]
+# (source, object name, extra flags); the iteration kernel's frame types and ranges of radii
+# (kRadiusGroups) are translation units of their own, the longest first.
+SOURCES = [("lk_iter_inst.hip", f"lk_iter_{t}_{g}", [f"-DOFMI_ITER_ELEM={t}", f"-DOFMI_ITER_GROUP={g}"])
+           for g in (0, 1, 2, 3, 4) for t in ("u8", "f32", "f16")]
+SOURCES += [(s + ".hip", s, []) for s in ("lk_iter", "pyramid", "runtime", "batch", "serve", "extras")]
 
 # Packed FP32 arithmetic is disabled for every HIP translation unit.
 HIPFLAGS = [
@@ -31,9 +34,10 @@ def hipcc() -> str:
     return exe
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *HIPFLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, name, flags = unit
+    obj = os.path.join(OBJ, name + ".o")
+    cmd = [hipcc(), *HIPFLAGS, *flags, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

@@ -64,6 +64,29 @@ __device__ __forceinline__ void st(__half* p, unsigned i, float x) {
   at(reinterpret_cast<unsigned short*>(p), i) = __half_as_ushort(__float2half_rn(x));
 }
 
+// A plane read through a buffer descriptor: element offset = a per-thread offset + a scalar one
+// (both below 2^30, as planes are), so a load whose row base is uniform costs no vector address
+// arithmetic.  The descriptor holds the plane's size; accesses past it read zero.
+template <typename T>
+struct Plane {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Plane(const T* p, int H, int W)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (int)((unsigned)(H * W) * (unsigned)sizeof(T)),
+                                            0x00027000)) {}
+  __device__ __forceinline__ float ld(unsigned off, int soff) const {
+    if constexpr (sizeof(T) == 1)
+      return (float)(unsigned)__builtin_amdgcn_raw_buffer_load_b8(r, (int)off, soff, 0);
+    else if constexpr (sizeof(T) == 2)
+      return __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(r, (int)(off * 2u), soff * 2, 0)));
+    else
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)(off * 4u), soff * 4, 0));
+  }
+  // Store to a float plane (an offset past it: dropped).
+  __device__ __forceinline__ void st(unsigned off, float x) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)(off * 4u), 0, 0);
+  }
+};
+
 // Row-major offset y * W + x with a 24-bit multiply: the full-rate v_mul_u32_u24 (the 32-bit
 // integer multiply issues at a quarter of the rate).  Plans keep H and W below 2^24 and H * W
 // below 2^30, so every product of an in-image row and a width fits.
@@ -109,52 +132,120 @@ __device__ __forceinline__ int split_coord(int x, float d, int n, float& frac, u
   return min(max(bu, 0), n - 1);
 }
 
-// I(x + u, y + v) by bilinear interpolation with clamped coordinates.
-template <typename T>
-__device__ __forceinline__ float warp_sample(const T* __restrict__ I, int H, int W, int x, int y,
-                                             float u, float v) {
-  float a, b;
-  unsigned sx, sy;
-  const int xi = split_coord(x, u, W, a, sx);
-  const int yi = split_coord(y, v, H, b, sy);
-  const unsigned o00 = rowofs(yi, W, xi);
-  const unsigned dy = sy * (unsigned)W;
-  const float z00 = ld(I, o00), z01 = ld(I, o00 + sx);
-  const float z10 = ld(I, o00 + dy), z11 = ld(I, o00 + dy + sx);
-  const float t = fmaf(a, z01 - z00, z00);
-  const float s = fmaf(a, z11 - z10, z10);
-  return fmaf(b, s - t, t);
+// x clamped to [0, hi] (hi uniform) in one instruction.
+__device__ __forceinline__ int clamp_i(int x, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(x), "s"(hi));
+  return r;
 }
 
-// Field value at in-image pixel (x, y) of the current level for the iteration's source.
-// The source mode is a compile-time parameter so every kernel reads its field straight-line.
-template <int MODE>
-__device__ __forceinline__ void read_flow(const IterArgs& a, int x, int y, float& u, float& v) {
-  if constexpr (MODE == kFlowSame) {
-    const unsigned i = rowofs(y, a.W, x);
-    u = at(a.uin, i);
-    v = at(a.vin, i);
-  } else if constexpr (MODE == kFlowCoarse) {
-    // 2 * bilinear(coarse, x/2, y/2): base floor(x/2), fraction 0 or 1/2.
-    const int x0 = x >> 1, y0 = y >> 1;
-    const unsigned dx = x0 < a.Wc - 1 ? 1u : 0u;
-    const unsigned dy = y0 < a.Hc - 1 ? (unsigned)a.Wc : 0u;
-    const float fa = (x & 1) ? 0.5f : 0.f, fb = (y & 1) ? 0.5f : 0.f;
-    const unsigned i00 = rowofs(y0, a.Wc, x0);
-    const unsigned i01 = i00 + dx, i10 = i00 + dy, i11 = i00 + dy + dx;
-    const float u00 = at(a.uin, i00), u01 = at(a.uin, i01), u10 = at(a.uin, i10), u11 = at(a.uin, i11);
-    const float v00 = at(a.vin, i00), v01 = at(a.vin, i01), v10 = at(a.vin, i10), v11 = at(a.vin, i11);
-    float t = fmaf(fa, u01 - u00, u00);
-    float s = fmaf(fa, u11 - u10, u10);
-    u = 2.f * fmaf(fb, s - t, t);
-    t = fmaf(fa, v01 - v00, v00);
-    s = fmaf(fa, v11 - v10, v10);
-    v = 2.f * fmaf(fb, s - t, t);
-  } else {
-    u = 0.f;
-    v = 0.f;
-  }
+// floor(d) as an integer, saturated (NaN: 0), in one instruction.
+__device__ __forceinline__ int floor_i(float d) {
+  int i;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(d));
+  return i;
 }
+
+// I(x + u, y + v) by bilinear interpolation with clamped coordinates, in two steps, so that a thread issues the loads of all its
+// samples before it waits for the first: issue() forms the coordinates and starts the four
+// loads, value() interpolates.
+template <typename T>
+struct Sample {
+  float z00, z01, z10, z11, a, b;
+  __device__ __forceinline__ void issue(const Plane<T>& I, int H, int W, int x, int y, float u, float v) {
+    unsigned sx, sy;
+    const int xi = split_coord(x, u, W, a, sx);
+    const int yi = split_coord(y, v, H, b, sy);
+    const unsigned o00 = rowofs(yi, W, xi);
+    const unsigned o10 = o00 + (sy ? (unsigned)W : 0u);
+    z00 = I.ld(o00, 0);
+    z01 = I.ld(o00 + sx, 0);
+    z10 = I.ld(o10, 0);
+    z11 = I.ld(o10 + sx, 0);
+  }
+  __device__ __forceinline__ float value() const {
+    const float t = fmaf(a, z01 - z00, z00);
+    const float s = fmaf(a, z11 - z10, z10);
+    return fmaf(b, s - t, t);
+  }
+};
+
+// 8-bit frames: the same value in fewer instructions.  The base is clamped to [0, n-2], so the
+// second tap always is the next pixel; the fraction measured from the clamped base, clamped to
+// [0, 1], is 0 before the image and 1 past it.  Along x the differences of 8-bit values are exact,
+// so a fraction of 1 gives the second tap exactly; along y the row results are rounded, and a base
+// past the image takes the second row by a select.  A frame one pixel wide or high keeps base and
+// fraction 0 along that axis (its second tap is any value; past the frame the plane reads 0).
+template <>
+struct Sample<uint8_t> {
+  float z00, z01, z10, z11, a, b;
+  bool below;
+  __device__ __forceinline__ void issue(const Plane<uint8_t>& I, int H, int W, int x, int y, float u, float v) {
+    const int bx = __builtin_elementwise_add_sat(x, floor_i(u));
+    const int by = __builtin_elementwise_add_sat(y, floor_i(v));
+    const int xi = clamp_i(bx, max(W - 2, 0)), yi = clamp_i(by, max(H - 2, 0));
+    a = __builtin_amdgcn_fmed3f(u - (float)(xi - x), 0.f, W >= 2 ? 1.f : 0.f);
+    b = __builtin_amdgcn_fmed3f(v - (float)(yi - y), 0.f, H >= 2 ? 1.f : 0.f);
+    below = by >= (H >= 2 ? H - 1 : 0x7fffffff);
+    const unsigned o = rowofs(yi, W, xi);
+    z00 = I.ld(o, 0);
+    z01 = I.ld(o + 1u, 0);
+    const int dy = H >= 2 ? W : 0;
+    z10 = I.ld(o, dy);
+    z11 = I.ld(o + 1u, dy);
+  }
+  __device__ __forceinline__ float value() const {
+    const float t = fmaf(a, z01 - z00, z00);
+    const float s = fmaf(a, z11 - z10, z10);
+    const float r = fmaf(b, s - t, t);
+    return below ? s : r;
+  }
+};
+
+// Field of a launch's source at K successive rows of one column, in two steps (loads, then the
+// values).  The source is a compile-time parameter, so every kernel reads its field straight-line.
+template <int MODE, int K>
+struct FieldRows {   // the previous iteration at the same level
+  float u[K], v[K];
+  __device__ __forceinline__ float2 at(int k, int, int) const { return make_float2(u[k], v[k]); }
+};
+template <int K>
+struct FieldRows<kFlowZero, K> {
+  __device__ __forceinline__ float2 at(int, int, int) const { return make_float2(0.f, 0.f); }
+};
+// The coarser level's Hc x Wc field: 2 * bilinear(coarse, x/2, y/2) at in-image pixel (x, y), base
+// floor(x/2), floor(y/2), fractions 0 or 1/2.  Two successive rows lie between the same two rows
+// of the coarser level (an even second row on the lower of them), so a pair takes eight loads.
+template <int K>
+struct FieldRows<kFlowCoarse, K> {
+  static constexpr int NP = (K + 1) / 2;
+  float u00[NP], u01[NP], u10[NP], u11[NP], v00[NP], v01[NP], v10[NP], v11[NP], fa;
+  // Pair p, whose first row is y.
+  __device__ __forceinline__ void issue(int p, const Plane<float>& U, const Plane<float>& V, int Hc, int Wc, int x,
+                                        int y) {
+    const int x0 = x >> 1, y0 = y >> 1;
+    const unsigned dx = x0 < Wc - 1 ? 1u : 0u;
+    const unsigned dy = y0 < Hc - 1 ? (unsigned)Wc : 0u;
+    fa = (x & 1) ? 0.5f : 0.f;
+    const unsigned i00 = rowofs(y0, Wc, x0);
+    const unsigned i01 = i00 + dx, i10 = i00 + dy, i11 = i00 + dy + dx;
+    u00[p] = U.ld(i00, 0), u01[p] = U.ld(i01, 0), u10[p] = U.ld(i10, 0), u11[p] = U.ld(i11, 0);
+    v00[p] = V.ld(i00, 0), v01[p] = V.ld(i01, 0), v10[p] = V.ld(i10, 0), v11[p] = V.ld(i11, 0);
+  }
+  __device__ __forceinline__ float value(float z00, float z01, float z10, float z11, bool lower, float fb) const {
+    const float t = fmaf(fa, z01 - z00, z00);
+    const float s = fmaf(fa, z11 - z10, z10);
+    return 2.f * (lower ? s : fmaf(fb, s - t, t));
+  }
+  // Row k, at image row y; ya: the first row of its pair.
+  __device__ __forceinline__ float2 at(int k, int y, int ya) const {
+    const int p = k / 2;
+    const bool lower = (y >> 1) != (ya >> 1);
+    const float fb = (y & 1) ? 0.5f : 0.f;
+    return make_float2(value(u00[p], u01[p], u10[p], u11[p], lower, fb),
+                       value(v00[p], v01[p], v10[p], v11[p], lower, fb));
+  }
+};
 
 // 1/x from the hardware reciprocal (1 ulp) refined by one Newton-Raphson step.
 __device__ __forceinline__ float recip(float x) {

@@ -107,6 +107,13 @@ inline bool tile_variant_valid(int variant, int R, bool gaussian) {
   return true;
 }
 
+// The iteration kernel's translation units: one per frame type and range of radii
+// [kRadiusGroups[g], kRadiusGroups[g+1]).
+constexpr int kRadiusGroups[] = {0, 4, 7, 9, 11, 13};
+template <typename T, int GROUP>
+hipError_t launch_iter_group(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb, int variant,
+                             hipStream_t s);
+
 // One fused Gauss-Newton iteration at one level (frames of element type `t`), tiles of height
 // (2R+1)*nb, tile variant `variant` (TileVariant).
 hipError_t launch_iter(Elem t, const IterArgs& a, int R, int nb, int variant, hipStream_t s);

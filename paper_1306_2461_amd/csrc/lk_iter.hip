@@ -6,16 +6,19 @@
 
 namespace ofmi {
 
-hipError_t launch_iter_u8(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb,
-                          int variant, hipStream_t s);
-hipError_t launch_iter_f32(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb,
-                          int variant, hipStream_t s);
-hipError_t launch_iter_f16(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb,
-                          int variant, hipStream_t s);
+#define OFMI_DECLARE_GROUP(T, G)                                                                     \
+  template <>                                                                                        \
+  hipError_t launch_iter_group<T, G>(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb, \
+                                     int variant, hipStream_t s);
+#define OFMI_DECLARE_ELEM(T)                                                          \
+  OFMI_DECLARE_GROUP(T, 0) OFMI_DECLARE_GROUP(T, 1) OFMI_DECLARE_GROUP(T, 2)          \
+  OFMI_DECLARE_GROUP(T, 3) OFMI_DECLARE_GROUP(T, 4)
+OFMI_DECLARE_ELEM(uint8_t)
+OFMI_DECLARE_ELEM(float)
+OFMI_DECLARE_ELEM(__half)
 
 int strip_width_for(int R) {
-  // Mirrors strip_width<R>(): the LDS footprint of 64-column strips stays within 64 KB for
-  // every supported radius (0..12).
+  // kStripWidth of the kernels, for every supported radius (0..12).
   (void)R;
   return 64;
 }
@@ -92,23 +95,38 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_iter(Elem t, const IterArgs& a, int R, int nb, int variant, hipStream_t s) {
-  switch (t) {
-    case Elem::U8: return launch_iter_u8(&a, nullptr, R, a.mode, nb, variant, s);
-    case Elem::F32: return launch_iter_f32(&a, nullptr, R, a.mode, nb, variant, s);
-    case Elem::F16: return launch_iter_f16(&a, nullptr, R, a.mode, nb, variant, s);
+namespace {
+
+template <typename T, int G = 0>
+hipError_t launch_elem(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb, int variant,
+                       hipStream_t s) {
+  if constexpr (G + 1 < (int)(sizeof(kRadiusGroups) / sizeof(int))) {
+    if (R >= kRadiusGroups[G] && R < kRadiusGroups[G + 1])
+      return launch_iter_group<T, G>(a, b, R, mode, nb, variant, s);
+    return launch_elem<T, G + 1>(a, b, R, mode, nb, variant, s);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_iter_batch(Elem t, const BatchLaunch& b, int R, int mode, hipStream_t s) {
-  if (b.ntiles <= 0) return hipSuccess;
+hipError_t launch_any(Elem t, const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb,
+                      int variant, hipStream_t s) {
   switch (t) {
-    case Elem::U8: return launch_iter_u8(nullptr, &b, R, mode, 0, b.variant, s);
-    case Elem::F32: return launch_iter_f32(nullptr, &b, R, mode, 0, b.variant, s);
-    case Elem::F16: return launch_iter_f16(nullptr, &b, R, mode, 0, b.variant, s);
+    case Elem::U8: return launch_elem<uint8_t>(a, b, R, mode, nb, variant, s);
+    case Elem::F32: return launch_elem<float>(a, b, R, mode, nb, variant, s);
+    case Elem::F16: return launch_elem<__half>(a, b, R, mode, nb, variant, s);
   }
   return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_iter(Elem t, const IterArgs& a, int R, int nb, int variant, hipStream_t s) {
+  return launch_any(t, &a, nullptr, R, a.mode, nb, variant, s);
+}
+
+hipError_t launch_iter_batch(Elem t, const BatchLaunch& b, int R, int mode, hipStream_t s) {
+  if (b.ntiles <= 0) return hipSuccess;
+  return launch_any(t, nullptr, &b, R, mode, 0, b.variant, s);
 }
 
 namespace {

@@ -3,12 +3,10 @@
 // gradients of the warped frame, the five window sums, the 2x2 solve and the update.
 //
 // Work decomposition (gfx950, wave64):
-//   * a workgroup of 5*TW threads (narrow) or at least 10*TW threads (wide, rounded up so the
-//     warped-frame positions of a band take few rounds per thread) owns a strip of TW output
-//     columns and TH output rows;
+//   * a workgroup owns a strip of TW output columns and TH output rows;
 //   * it walks down the strip in bands of N = 2r+1 product rows; per band:
-//       P1  warped frame for the band's new rows into an LDS ring; all global loads of the
-//           band (field, frame 1, centre field of the band's outputs) are issued here;
+//       P1  warped frame of the band's new rows into LDS: a thread owns K1 successive rows of
+//           one column, and the field it needs is in flight since P2 of the band before;
 //       P2  the five products Ix^2, IxIy, Iy^2, Ix It, Iy It of the band's rows into LDS;
 //       P3  horizontal window sums: one thread per (channel, row, 8-column segment); every
 //           window of a segment holds one common column, so each window is a suffix sum plus
@@ -22,11 +20,24 @@
 //           direct weighted sum over the same rows for the Gaussian-weighted window;
 //       P5  per-pixel 2x2 solve and update for the band's output rows.
 //   The window sums therefore do not depend on how the image is cut into tiles.
-//   * two-bands-per-pass variants run the five phases once over two bands' rows with twice
-//     the threads (20*TW), so a one-band tile (output band plus priming band) is one trip;
-//   * coarse-field launches of the wide one-band variants keep the interpolated field of the
-//     warped-frame positions in an LDS ring for P2 and P5.
+//   * two-bands-per-pass variants run the five phases once over two bands' rows, so a one-band
+//     tile (output band plus priming band) is one trip.
+//
+// What bounds it: vector instructions and the waits between the five phases; HBM is at about
+// half of what a copy reaches.  Two workgroups per CU hide each other's barriers and load rounds,
+// which asks for at most 80 registers per thread (three waves per SIMD each) and no scratch: a
+// third of the vector instructions of an earlier form went into per-item index arithmetic, and
+// variants that kept more in flight (samples gathered a band ahead) spilled or fell to one
+// workgroup per CU and were slower.  Measured on level 0 of 16 pairs of 1024^2 (r = 8, uint8, tiles
+// of 16 bands, iterations of a level averaged): 139.8 us per launch before the per-column mapping,
+// 8-bit samples and paired coarse rows below, 119.5 us with them (16.8 Mpx: 2.5 TB/s of algorithmic
+// bytes); a plan's 2048^2 level 0 (8 bands) 42.9 -> 32.1 us.  Vector memory instructions cost by
+// form, not by bytes: 64 lanes at unit stride 4.7 clocks per CU (bytes or dwords), 64-bit, stride-2
+// or unaligned 16-bit lanes 16 clocks, so every load and store here is one element per lane at unit
+// stride and a bilinear tap pair is two byte loads.
 #pragma once
+
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -41,24 +52,29 @@ __device__ __forceinline__ void add_count(unsigned long long* dst, unsigned c) {
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(dst, (unsigned long long)c);
 }
 
-// Threads per workgroup.  Narrow variants: 5 per output column.  Wide variants: at least 10
-// per column, and enough that the warped-frame positions of a steady pass (every pass but a
-// tile's first, which also samples the two rows above) take the fewest rounds of items per
-// thread that a workgroup of at most 1024 allows, rounded up to whole groups of four waves (one
-// per SIMD of the CU): e.g. r = 8 on 64-column strips samples 17 x 82 positions per band, 3
-// rounds at 640 threads (73 % of the lanes busy) and 2 at 768; on 32-column strips 17 x 50
-// positions, one round at 1024.
+// Threads of a workgroup own K1 successive rows of one column of a band's warped frame (WC =
+// TW + 2R + 2 columns), so a thread's column, clamps and LDS offsets are formed once per tile, its
+// global offset is a per-thread constant added to a scalar row base, and P2 finds part of the
+// warped values and fields it needs in the thread's own registers.
+// Wide variants: the fewest rows per thread that a workgroup of at most 768 allows (three waves
+// per SIMD: two workgroups share a CU), rounded up to whole groups of four waves, one per SIMD:
+// e.g. r = 8 on 64-column strips samples 17 rows of 82 positions per band, two rows per thread at
+// 768 threads.  From r = 9 on 64-column strips would take three rows per thread, which spills at
+// the 80 registers of two workgroups per CU: one workgroup of up to 1024 there.  Narrow variants:
+// at least 5 threads per output column.
+template <int R, int TW, bool WIDE, int BB>
+constexpr bool two_groups() {
+  return WIDE && !(R > 8 && TW > 32);
+}
 template <int R, int TW, bool WIDE, int BB>
 constexpr int group_threads() {
-  if (!WIDE) return 5 * TW * BB;
   const int N = 2 * R + 1, WC = TW + 2 * R + 2;
-  const int items = (BB == 1 ? N : BB * N + 2) * WC;
-  const int base = 10 * TW * BB;
-  const int k = (items + 1023) / 1024;
-  int nt = ((items + k - 1) / k + 255) / 256 * 256;
-  if (nt < base) nt = base;
-  if (nt > 1024) nt = base;
-  return nt;
+  const int rows = BB == 1 ? N : BB * N + 2;
+  if (!WIDE) return 5 * TW * BB;
+  int k = 1;
+  while ((rows + k - 1) / k * WC > (two_groups<R, TW, WIDE, BB>() ? 768 : 1024)) ++k;
+  const int nt = ((rows + k - 1) / k * WC + 255) / 256 * 256;
+  return nt < 5 * TW ? 5 * TW : nt;
 }
 
 template <int R, int TW_, bool WIDE = false, int BB = 1>
@@ -71,60 +87,46 @@ struct Cfg {
   static constexpr int WC = PC + 2;                   // warped-frame columns
   static constexpr int HL = 8 + 2 * R;                // products read per horizontal segment
   static constexpr int HL4 = (HL + 3) / 4;            // ... in float4 units
-  static constexpr int PP = ((TW + 4 * HL4 - 8) + 3) / 4 * 4 + 4;  // product row pitch
+  // Row pitches of the products and of the window sums: an odd number of 16-byte words, so the
+  // 128-bit reads and writes of P3, whose lanes take successive rows, spread over all banks.
+  static constexpr int PP = (TW + 4 * HL4 - 8 + 3) / 8 * 8 + 4;
+  static constexpr int HP = TW + 4;
   static constexpr int WP = WC + 1;                   // warped-frame row pitch
-  // Warped-frame rows held in LDS: one band per pass keeps a power-of-two ring (the two rows
-  // shared with the next band stay); two bands per pass sample all NR + 2 rows every pass.
-  static constexpr int RING = N + 2 <= 16 ? 16 : 32;
-  static constexpr int WROWS = BB == 1 ? RING : NR + 2;
+  // Warped-frame rows held in LDS: the rows -1 .. NR of the pass.  With one band per pass the
+  // last two are moved to the front for the next pass instead of being sampled again.
+  static constexpr int P1_ROWS = BB == 1 ? N : NR + 2;          // rows sampled per pass
+  static constexpr int P1_FIRST = BB == 1 ? 2 : 0;              // ... from this LDS row
   static constexpr int NSEG = TW / 8;
-  static constexpr int P1_ROWS_MAX = NR + 2;
-  static constexpr int K1 = (P1_ROWS_MAX * WC + NT - 1) / NT;   // P1 items per thread
-  // ... in a pass after a tile's first (one band per pass: N new rows)
-  static constexpr int K1S = ((BB == 1 ? N : P1_ROWS_MAX) * WC + NT - 1) / NT;
-  static constexpr int K2 = (NR * PC + NT - 1) / NT;            // P2 items per thread
+  static constexpr int K1 = (P1_ROWS + NT / WC - 1) / (NT / WC);  // rows per thread in P1, P2
+  static constexpr int G = (P1_ROWS + K1 - 1) / K1;             // threads per column
+  // (a thread's rows past the last one are sampled too, into LDS rows that nothing reads)
+  static constexpr int W2ROWS = P1_FIRST + G * K1;
   static constexpr int K3 = (5 * NR * NSEG + NT - 1) / NT;      // P3 items per thread
-  static constexpr int K5 = (NR * TW + NT - 1) / NT;            // P5 items per thread
-  // The window sums [5][NR][TW] reuse the product buffer [5][NR][PP] once P3 has read it, or
-  // (SPLIT) have a region of their own after the warped rows, which saves P3's second barrier.
-  static constexpr size_t LDS_FLOATS = 5 * (size_t)NR * PP + (size_t)WROWS * WP;
-  static constexpr size_t HS_FLOATS = 5 * (size_t)NR * TW;
-  // Field ring (launches that read a field, one band per pass): u and v of the warped-frame
-  // positions, kept for FRING rows so that P2 and P5 read them from LDS instead of loading
-  // (and, from a coarser field, re-interpolating) them again.
-  static constexpr int FRING = 64;
-  static constexpr size_t FR_FLOATS = 2 * (size_t)FRING * WP;
-  static constexpr bool SPLIT_FITS = (LDS_FLOATS + HS_FLOATS) * sizeof(float) <= 65536;
+  static constexpr int RG = NT / TW;                            // P5 rows per round
+  static constexpr int K5 = (NR + RG - 1) / RG;                 // P5 rounds
+  static_assert(NT >= WC && G * WC <= NT && NT % TW == 0 && 2 * WP <= NT,
+                "workgroup too small for the strip");
+  // LDS: products [5][NR][PP], warped rows, window sums [5][NR][HP], and the field rows that P2
+  // reads from another thread: u and v of each thread's last row, [G][WP] each.
+  static constexpr size_t PR_FLOATS = 5 * (size_t)NR * PP;
+  static constexpr size_t W2_FLOATS = ((size_t)W2ROWS * WP + 3) / 4 * 4;
+  static constexpr size_t HS_FLOATS = 5 * (size_t)NR * HP;
+  static constexpr size_t FC_FLOATS = 2 * (size_t)G * WP;
+  static constexpr size_t LDS_BYTES = (PR_FLOATS + W2_FLOATS + HS_FLOATS + FC_FLOATS) * sizeof(float);
 };
 
-// Separate window-sum region for the wide (latency) variant where it fits in 64 KB: that
-// variant runs about one workgroup per CU, so the larger LDS footprint costs no occupancy.
-template <int R, int TW, bool WIDE, bool LEAN, int BB = 1>
-constexpr bool split_hs() {
-  return WIDE && !LEAN && Cfg<R, TW, WIDE, BB>::SPLIT_FITS;
-}
-template <int R, int TW, bool WIDE, bool LEAN, int BB = 1, bool FR = false>
-constexpr size_t lds_bytes() {
-  using C = Cfg<R, TW, WIDE, BB>;
-  return (C::LDS_FLOATS + (split_hs<R, TW, WIDE, LEAN, BB>() ? C::HS_FLOATS : 0) +
-          (FR ? C::FR_FLOATS : 0)) * sizeof(float);
-}
-// Plain launches of the wide variants with one band per pass keep the field ring when they
-// read a field (its 2*64 rows cost LDS that only these latency-bound launches can spare); the
-// batched kernel keeps it in every variant (measured faster there as well).
-template <int MODE, bool WIDE, bool LEAN, int BB>
-constexpr bool field_ring() {
-  return MODE != kFlowZero && WIDE && !LEAN && BB == 1;
+// Wavefronts per SIMD the register allocation aims at: two workgroups of a wide variant share a
+// CU (one's barriers and load rounds hide behind the other's arithmetic), which leaves 80
+// registers per thread at three waves per SIMD each (from r = 11 the window rows of P4 need more).
+template <int R, int TW, bool WIDE, int BB>
+constexpr int waves_per_simd() {
+  return two_groups<R, TW, WIDE, BB>() && R <= 10 ? 2 * ((Cfg<R, TW, WIDE, BB>::NT + 255) / 256) : 1;
 }
 
 // One tile: TW output columns from x0 = bx*TW and TH output rows from row y0, walked in
 // nbands bands (TH is a multiple of N; nbands = TH/N + 1).  `sm4` is the workgroup's LDS.
 // INTERIOR: the tile's whole warped-frame region (the tile grown by r + 1 px, all bands)
 // lies inside the image, so no position needs clamping or an in-image test.
-// LEAN: the item indices are recomputed every band instead of being kept in registers
-// across the band loop: a few more VALU instructions per band for far fewer live registers,
-// i.e. more resident workgroups per CU (launches with many tiles); without it each band's
-// dependent path is shorter (launches with about one tile per CU).
 // pixel_mask: the tile holds masked pixels, whose flow is written as zero.
 // GAUSS: window sums weighted by the separable taps a.taps[0..2r] (Gaussian-weighted window)
 // instead of the unweighted box: every horizontal and vertical sum is a direct 2r+1-term
@@ -134,42 +136,83 @@ constexpr bool field_ring() {
 // threads, so a tile of two bands (one output band and the band that primes the vertical
 // sums) is one pass of the dependent path instead of two; P4 walks the two bands in order,
 // with the same additions as two single-band passes.  nbands is then even.
-// FR (a field is read, one band per pass): P1 stores the field of every warped-frame position
-// (interpolated from the coarser level in the coarse-field mode) in a ring of FRING rows; P2
-// and P5 read theirs from it (the same value at the same clamped position) instead of loading
-// it again (eight loads per value from a coarser field, one from the current one).  The next band's P1 may overwrite
-// ring rows while slower threads are still in P5: it writes rows tb+N+1 .. tb+2N while P5
-// reads rows tb-R .. tb+R, at most 5R+2 < FRING apart, so no slot is shared.
-template <typename T, int R, int TW, int MODE, bool WIDE, bool DEFER, bool INTERIOR, bool LEAN,
-          bool GAUSS = false, int BB = 1, bool FR = false, bool BUB = false>
+template <typename T, int R, int TW, int MODE, bool WIDE, bool INTERIOR, bool GAUSS, int BB,
+          bool BUB>
 __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands, int bx, int y0,
                                            bool pixel_mask, float4* sm4) {
   using C = Cfg<R, TW, WIDE, BB>;
-  constexpr int N = C::N, NR = C::NR, NT = C::NT, PC = C::PC, WC = C::WC, PP = C::PP, WP = C::WP;
-  constexpr int RMASK = C::RING - 1;
+  constexpr int N = C::N, NR = C::NR, NT = C::NT, PC = C::PC, WC = C::WC, PP = C::PP, WP = C::WP,
+                HP = C::HP, K1 = C::K1, G = C::G, F0 = C::P1_FIRST;
+  constexpr bool FLOW = MODE != kFlowZero;
   static_assert(BB == 1 || BB == 2, "one or two bands per pass");
-  static_assert(!FR || (MODE != kFlowZero && BB == 1 && 5 * R + 2 < C::FRING),
-                "field ring: launches that read a field, one band per pass");
-  float* sm = reinterpret_cast<float*>(sm4);
-  constexpr bool kSplit = split_hs<R, TW, WIDE, LEAN, BB>();
-  float* pr = sm;                               // [5][NR][PP] products (16-byte aligned rows)
-  float* w2 = pr + 5 * NR * PP;                 // [WROWS][WP] warped frame
-  // [5][NR][TW] horizontal, then window sums (16-byte aligned: WROWS*WP is a multiple of 4
-  // here or the region aliases the products)
-  float* hs = kSplit ? w2 + C::WROWS * WP : pr;
-  float* fru = kSplit ? hs + C::HS_FLOATS : w2 + C::WROWS * WP;   // [FRING][WP] (FR only)
-  float* frv = fru + C::FRING * WP;
-  constexpr int FMASK = C::FRING - 1;
+  float* pr = reinterpret_cast<float*>(sm4);    // [5][NR][PP] products (16-byte aligned rows)
+  float* w2 = pr + C::PR_FLOATS;                // [W2ROWS][WP] warped frame from row tb-1
+  float* hs = w2 + C::W2_FLOATS;                // [5][NR][HP] horizontal, then window sums
+  float* fcu = hs + C::HS_FLOATS;               // [G][WP] field rows passed on to P2
+  float* fcv = fcu + G * WP;
 
-  const int tid0 = threadIdx.x;
+  // Opaque per tile, so that a work-list kernel forms what depends on it per tile instead of
+  // keeping it in registers across the tiles of both paths.
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int H = a.H, W = a.W;
   const int x0 = bx * TW;
-  const T* __restrict__ I1 = (const T*)a.I1;
-  const T* __restrict__ I2 = (const T*)a.I2;
+  const Plane<T> I1((const T*)a.I1, H, W), I2((const T*)a.I2, H, W);
+  const Plane<float> U(a.uin, MODE == kFlowCoarse ? a.Hc : H, MODE == kFlowCoarse ? a.Wc : W);
+  const Plane<float> V(a.vin, MODE == kFlowCoarse ? a.Hc : H, MODE == kFlowCoarse ? a.Wc : W);
+  const Plane<float> UO(a.uout, H, W), VO(a.vout, H, W);
+
+  // This thread's column of the warped frame and its first row of a pass (threads past the last
+  // group repeat that group: the same values to the same slots).
+  using DW = ConstDiv<WC, NT>;
+  const int gq = (int)DW::q((unsigned)tid), lx = (int)DW::r((unsigned)tid, (unsigned)gq);
+  const int gc = min(gq, G - 1), g = gc * K1;
+  const int gx = INTERIOR ? x0 - R - 1 + lx : min(max(x0 - R - 1 + lx, 0), W - 1);
+  const bool pcol_in = INTERIOR || (x0 - R - 1 + lx >= 0 && x0 - R - 1 + lx < W);
+  const bool p2 = lx >= 1 && lx <= PC && gq < G;
+  constexpr int kLast = (G - 1) * K1;            // the last group's first row
+  constexpr int kEnd = C::P1_ROWS - 1 - kLast;   // its last row
+  // Image row i from image row ys (clamped).
+  auto row_at = [&](int ys, int i) { return INTERIOR ? ys + i : min(max(ys + i, 0), H - 1); };
+  // Element (gx, row i from image row ys) of a plane: interior tiles add a scalar row base to a
+  // per-thread offset.
+  auto elem = [&](const auto& p, int ys, int i) {
+    if constexpr (INTERIOR)
+      return p.ld(__umul24((unsigned)i, (unsigned)W) + (unsigned)lx, ys * W + x0 - R - 1);
+    else
+      return p.ld(rowofs(row_at(ys, i), W, gx), 0);
+  };
+  // Field at column gx of K rows from row i of the rows from image row ys: loads, and row k's value.
+  auto field = [&](auto& f, int ys, int i, auto rows) {
+    constexpr int K = decltype(rows)::value;
+    if constexpr (MODE == kFlowSame) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        f.u[k] = elem(U, ys + k, i);
+        f.v[k] = elem(V, ys + k, i);
+      }
+    } else if constexpr (MODE == kFlowCoarse) {
+#pragma unroll
+      for (int k = 0; k < K; k += 2) f.issue(k / 2, U, V, a.Hc, a.Wc, gx, min(row_at(ys + k, i), H - 1));
+    }
+  };
+  auto field_at = [&](const auto& f, int ys, int i, int k) {
+    return f.at(k, min(row_at(ys + k, i), H - 1), min(row_at(ys + k / 2 * 2, i), H - 1));
+  };
+  // Frame 1 one row above this thread's k-th row of the pass whose LDS row 0 is image row yw.
+  auto frame1 = [&](int yw, int k) {
+    if (F0 == 0 && k == 0) return elem(I1, yw, max(g - 1, 0));
+    return elem(I1, yw + F0 + k - 1, g);
+  };
+  using S = Sample<T>;
 
   // P4 ownership: channel and column of this thread (the first 5*TW threads).
-  const int vk = tid0 / TW, vc = tid0 - vk * TW;
+  const int vk = tid / TW, vc = tid - vk * TW;
   const bool p4 = vk < 5;
+  // P5 ownership: output column and row of a round (the row is uniform over a wave on
+  // 64-column strips).
+  const int oc = tid % TW, orow = TW == 64 ? __builtin_amdgcn_readfirstlane(tid / TW) : tid / TW;
+  const int ogx = INTERIOR ? x0 + oc : min(x0 + oc, W - 1);
   float prev[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) prev[i] = 0.f;
@@ -179,189 +222,196 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   const bool bub = BUB && a.bcount != nullptr;
   const float bthr = bub ? at(a.bthr, 0u) : 0.f;
   unsigned bcnt = 0;
+
+  // Field rows passed on: thread group q reads slot q, the field at the row above its first:
+  // the last row of group q-1 of the pass, for group 0 the last row of the pass before, which
+  // the last group keeps in registers until then.
+  float lu = 0.f, lv = 0.f;
+  auto keep_field = [&](const float* fu, const float* fv, bool first) {
+    if constexpr (FLOW) {
+      const bool end = gc == G - 1;
+      if (!(first && end)) {
+        const int s = (end ? 0 : gc + 1) * WP + lx;
+        fcu[s] = end ? lu : fu[K1 - 1];
+        fcv[s] = end ? lv : fv[K1 - 1];
+      }
+      lu = fu[kEnd];
+      lv = fv[kEnd];
+    }
+  };
+
+  // Field at this thread's output pixel of round k (clamped row: one outside the tile or the
+  // image is loaded and not used).
+  auto centre = [&](FieldRows<MODE, 1>& c, int tb, int k) {
+    const int gy = min(max(y0 + tb - 2 * R + C::RG * k + orow, 0), H - 1);
+    if constexpr (MODE == kFlowCoarse) {
+      c.issue(0, U, V, a.Hc, a.Wc, ogx, gy);
+    } else if constexpr (MODE == kFlowSame) {
+      c.u[0] = U.ld(rowofs(gy, W, ogx), 0);
+      c.v[0] = V.ld(rowofs(gy, W, ogx), 0);
+    }
+  };
+  // P5 of the pass whose first product row is tb: 2x2 solve and update of its output rows, with
+  // the field c at this thread's output pixels.  Lanes without an output pixel store past the
+  // plane (dropped), so that the number of stores in flight is known where the samples issued
+  // before them are waited for.
+  auto solve = [&](int tb, FieldRows<MODE, 1>* c) {
+#pragma unroll
+    for (int k = 0; k < C::K5; ++k) {
+      const int r = orow + C::RG * k, j = tb + r - 2 * R;   // row of the pass, of the tile
+      if (C::RG * (k + 1) > NR && r >= NR) continue;
+      __builtin_amdgcn_sched_barrier(0);   // one round's registers at a time
+      if constexpr (MODE == kFlowCoarse) centre(c[k], tb, k);
+      const int gy = y0 + j;
+      const bool out = j >= 0 && j < TH && (INTERIOR || (x0 + oc < W && gy < H));
+      const float* s = hs + r * HP + oc;
+      const float2 f5 = c[k].at(0, gy, gy);
+      float un, vn;
+      solve_update(s[0], s[NR * HP], s[2 * NR * HP], s[3 * NR * HP], s[4 * NR * HP], f5.x, f5.y,
+                   un, vn);
+      const unsigned o = rowofs(gy, W, x0 + oc);
+      if (pixel_mask) {   // masked-out pixels: zero flow
+        if (out && at(a.mask, o) == 0) un = vn = 0.f;
+      }
+      UO.st(out ? o : 0x3fffffffu, un);
+      VO.st(out ? o : 0x3fffffffu, vn);
+      if constexpr (BUB) {
+        if (bub) bcnt += out && un <= bthr ? 1u : 0u;
+      }
+    }
+  };
+  // The field at a pass's warped-frame rows: a same-level launch loads it during P4 of the pass
+  // before (ahead of that pass's stores, which a later load would be waited for with), a
+  // coarse-field launch, whose values take eight loads each, in P1.
+  constexpr bool AHEAD = MODE == kFlowSame;
+  constexpr std::integral_constant<int, K1> kRows{};
+  FieldRows<MODE, K1> f;
+  if constexpr (AHEAD) field(f, y0 - R - 1 + F0, g, kRows);
   for (int b = 0; b < nbands; b += BB) {
     const int tb = N * b;                        // first product row of the pass
-    // LEAN: the thread index is re-materialised per band, opaque to the optimiser, so the
-    // item indices derived from it are not hoisted out of the loop.
-    int tid = tid0;
-    if constexpr (LEAN) asm volatile("" : "+v"(tid));
-    // ---------------------------------------------------------------- P1
-    // Every global load of the band is issued here, branch-free (clamped addresses; results
-    // for items outside the image or the band are discarded): the field at the warped-frame
-    // positions, the four frame-2 samples of every warped-frame position, then frame 1 and the
-    // field at this thread's P2 items and the centre field of its P5 items.  In the lean
-    // variants a scheduling barrier keeps the last group after the samples are stored: issued
-    // together the groups are all live at once (the kernel's register peak); the split costs
-    // one more dependent load round per band and buys resident workgroups.
-    const int wfirst = (BB == 2 || b == 0) ? tb - 1 : tb + 1;
-    const int nw = ((BB == 2 || b == 0) ? NR + 2 : N) * WC;
-    int wofs[C::K1], wgx[C::K1], wgy[C::K1];
-    float wu[C::K1], wv[C::K1];
+    const int yw = y0 - R - 1 + tb;              // image row of LDS row 0
+    const bool more = b + BB < nbands;
+    // ------------------------------------------------------------------ P1
+    // Branch-free loads (clamped addresses).  In a tile's first band the two rows above it (LDS
+    // rows 0 and 1) are sampled here too.
+    float wu[K1], wv[K1], i1v[K1], wval[K1];
+    {
+      const bool ext = BB == 1 && b == 0 && tid < 2 * WC;
+      FieldRows<MODE, 1> ef;
+      if (ext) field(ef, yw, gq, std::integral_constant<int, 1>{});
+      if constexpr (!AHEAD) field(f, yw + F0, g, kRows);
 #pragma unroll
-    for (int k = 0; k < C::K1; ++k) {
-      if (k >= C::K1S && b != 0) break;   // uniform: only a tile's first pass has these
-      using DW = ConstDiv<WC, C::P1_ROWS_MAX * WC>;
-      const unsigned i = (unsigned)min(tid + k * NT, nw - 1), qi = DW::q(i);
-      const int w = wfirst + (int)qi, lx = (int)DW::r(i, qi);
-      if constexpr (INTERIOR) {
-        wgx[k] = x0 - R - 1 + lx;
-        wgy[k] = y0 - R + w;
-      } else {
-        wgx[k] = min(max(x0 - R - 1 + lx, 0), W - 1);
-        wgy[k] = min(max(y0 - R + w, 0), H - 1);
-      }
-      wofs[k] = (BB == 1 ? (w & RMASK) : w - (tb - 1)) * WP + lx;
-      read_flow<MODE>(a, wgx[k], wgy[k], wu[k], wv[k]);
-      if constexpr (FR) {
-        fru[(w & FMASK) * WP + lx] = wu[k];
-        frv[(w & FMASK) * WP + lx] = wv[k];
-      }
-    }
-    // In the coarse-field mode each field value costs eight loads: where registers are tight
-    // (DEFER) the field at this thread's P2 and P5 items is read in those phases rather than
-    // held in flight here.
-    constexpr bool kDefer = DEFER && MODE == kFlowCoarse && !FR;
-    constexpr bool kLoadField = !kDefer && !FR;   // P2/P5 field loads issued in P1
-    float i1v[C::K2], pu[C::K2], pv[C::K2];
-    float cu[C::K5], cv[C::K5];
-    // (The same loads are written twice, before the samples for the default variants and
-    // after them for the lean ones, so that each keeps its own straight-line schedule.)
-    if constexpr (!LEAN) {
+      for (int k = 0; k < K1; ++k) i1v[k] = frame1(yw, k);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < C::K2; ++k) {
-        using DP = ConstDiv<PC, NR * PC>;
-        const unsigned i = (unsigned)min(tid + k * NT, NR * PC - 1), qi = DP::q(i);
-        int gx = x0 - R + (int)DP::r(i, qi), gy = y0 - R + tb + (int)qi;
-        if constexpr (!INTERIOR) {
-          gx = min(max(gx, 0), W - 1);
-          gy = min(max(gy, 0), H - 1);
+      for (int k = 0; k < K1; ++k) {
+        const float2 w = field_at(f, yw + F0, g, k);
+        wu[k] = w.x;
+        wv[k] = w.y;
+      }
+      float eu = 0.f, ev = 0.f;
+      S smp[K1], es;
+      if (ext) {
+        const float2 w = field_at(ef, yw, gq, 0);
+        eu = w.x;
+        ev = w.y;
+        es.issue(I2, H, W, gx, row_at(yw, gq), eu, ev);
+      }
+#pragma unroll
+      for (int k = 0; k < K1; ++k) smp[k].issue(I2, H, W, gx, row_at(yw + F0 + k, g), wu[k], wv[k]);
+      __builtin_amdgcn_sched_barrier(0);
+      keep_field(wu, wv, b == 0);
+      if (ext) {
+        if (FLOW && gq == 1) {
+          fcu[lx] = eu;
+          fcv[lx] = ev;
         }
-        i1v[k] = ld(I1, rowofs(gy, W, gx));
-        if constexpr (kLoadField) read_flow<MODE>(a, gx, gy, pu[k], pv[k]);
+        w2[gq * WP + lx] = es.value();
       }
-      if constexpr (kLoadField) {
 #pragma unroll
-        for (int k = 0; k < C::K5; ++k) {
-          const int i = min(tid + k * NT, NR * TW - 1);
-          const int gx = INTERIOR ? x0 + (int)((unsigned)i % TW) : min(x0 + (int)((unsigned)i % TW), W - 1);
-          const int gy = min(max(y0 + tb + (int)((unsigned)i / TW) - 2 * R, 0), H - 1);
-          read_flow<MODE>(a, gx, gy, cu[k], cv[k]);
-        }
-      }
-    }
-    // Items past the end repeat the last position (clamped index) and store the identical
-    // value to the identical slot, so the stores need no guard: a guard lets the compiler
-    // sink each item's gathers into its own branch and wait for them one item at a time.
-#pragma unroll
-    for (int k = 0; k < C::K1; ++k) {
-      if (k >= C::K1S && b != 0) break;
-      w2[wofs[k]] = warp_sample(I2, H, W, wgx[k], wgy[k], wu[k], wv[k]);
-    }
-    if constexpr (LEAN) {
-      __builtin_amdgcn_sched_barrier(0);   // compiler-only fence
-#pragma unroll
-      for (int k = 0; k < C::K2; ++k) {
-        using DP = ConstDiv<PC, NR * PC>;
-        const unsigned i = (unsigned)min(tid + k * NT, NR * PC - 1), qi = DP::q(i);
-        int gx = x0 - R + (int)DP::r(i, qi), gy = y0 - R + tb + (int)qi;
-        if constexpr (!INTERIOR) {
-          gx = min(max(gx, 0), W - 1);
-          gy = min(max(gy, 0), H - 1);
-        }
-        i1v[k] = ld(I1, rowofs(gy, W, gx));
-        if constexpr (kLoadField) read_flow<MODE>(a, gx, gy, pu[k], pv[k]);
-      }
-      if constexpr (kLoadField) {
-#pragma unroll
-        for (int k = 0; k < C::K5; ++k) {
-          const int i = min(tid + k * NT, NR * TW - 1);
-          const int gx = INTERIOR ? x0 + (int)((unsigned)i % TW) : min(x0 + (int)((unsigned)i % TW), W - 1);
-          const int gy = min(max(y0 + tb + (int)((unsigned)i / TW) - 2 * R, 0), H - 1);
-          read_flow<MODE>(a, gx, gy, cu[k], cv[k]);
-        }
+      for (int k = 0; k < K1; ++k) {
+        wval[k] = smp[k].value();
+        w2[(g + F0 + k) * WP + lx] = wval[k];
       }
     }
     __syncthreads();
-    // ---------------------------------------------------------------- P2
-    if constexpr (kDefer) {
-#pragma unroll
-      for (int k = 0; k < C::K2; ++k) {
-        using DP = ConstDiv<PC, NR * PC>;
-        const unsigned i = (unsigned)min(tid + k * NT, NR * PC - 1), qi = DP::q(i);
-        int gx = x0 - R + (int)DP::r(i, qi), gy = y0 - R + tb + (int)qi;
-        if constexpr (!INTERIOR) {
-          gx = min(max(gx, 0), W - 1);
-          gy = min(max(gy, 0), H - 1);
-        }
-        read_flow<MODE>(a, gx, gy, pu[k], pv[k]);
-      }
+    // ------------------------------------------------------------------ P2
+    if constexpr (AHEAD) {
+      if (more) field(f, yw + NR + F0, g, kRows);
     }
+    // The products one row above each of this thread's warped rows: the row below is the
+    // thread's own, the centre and the row above too from its second and third row on.
+    if (p2) {
+      constexpr int kSkip = 2 - F0;   // with two bands per pass rows -1 and 0 have no product above
+      const float* wr = w2 + (g + F0) * WP + lx;   // this thread's first warped row
+      const int up = kSkip == 0 || g > 0 ? 1 : 0;
+      float c1 = wr[-up * WP], c2 = wr[-2 * up * WP];   // one, two rows above
+      float fu = 0.f, fv = 0.f;       // field at the product position
+      if constexpr (FLOW) {
+        fu = fcu[gc * WP + lx];
+        fv = fcv[gc * WP + lx];
+      }
 #pragma unroll
-    for (int k = 0; k < C::K2; ++k) {
-      const int i = tid + k * NT;
-      if (i < NR * PC) {
-        using DP = ConstDiv<PC, NR * PC>;
-        const int r = (int)DP::q((unsigned)i), c = (int)DP::r((unsigned)i, (unsigned)r);
-        const int t = tb + r;
-        const int gx = x0 - R + c, gy = y0 - R + t;
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f, p4 = 0.f;
-        if (INTERIOR || (gx >= 0 && gx < W && gy >= 0 && gy < H)) {
-          // warped row t sits in ring slot t & RMASK, or (two bands per pass) in row r + 1
-          const int s0 = BB == 1 ? t & RMASK : r + 1;
-          const int sm1 = BB == 1 ? (t - 1) & RMASK : r;
-          const int sp1 = BB == 1 ? (t + 1) & RMASK : r + 2;
-          const float* row = w2 + s0 * WP + c + 1;
-          const float ix = 0.5f * (row[1] - row[-1]);
-          const float iy = 0.5f * (w2[sp1 * WP + c + 1] - w2[sm1 * WP + c + 1]);
-          float fu, fv;   // field at the product position
-          if constexpr (FR) {
-            fu = fru[(t & FMASK) * WP + c + 1];
-            fv = frv[(t & FMASK) * WP + c + 1];
-          } else {
-            fu = pu[k];
-            fv = pv[k];
-          }
-          float it = row[0] - i1v[k];
+      for (int k = 0; k < K1; ++k) {
+        if ((kSkip == 0 || g + k >= kSkip) && (kLast + k < C::P1_ROWS || g + k < C::P1_ROWS)) {
+          const int r = g + k - kSkip;
+          const float* row = wr + (k - 1) * WP;
+          float ix = 0.5f * (row[1] - row[-1]);
+          float iy = 0.5f * (wval[k] - c2);
+          float it = c1 - i1v[k];
           it = fmaf(-ix, fu, it);
           it = fmaf(-iy, fv, it);
-          p0 = ix * ix;
-          p1 = ix * iy;
-          p2 = iy * iy;
-          p3 = ix * it;
-          p4 = iy * it;
+          if constexpr (!INTERIOR) {   // no product outside the image
+            const int gy = yw + 1 + r;
+            const bool in = pcol_in && gy >= 0 && gy < H;
+            ix = in ? ix : 0.f;
+            iy = in ? iy : 0.f;
+            it = in ? it : 0.f;
+          }
+          float* q = pr + r * PP + lx - 1;
+          q[0] = ix * ix;
+          q[NR * PP] = ix * iy;
+          q[2 * NR * PP] = iy * iy;
+          q[3 * NR * PP] = ix * it;
+          q[4 * NR * PP] = iy * it;
         }
-        float* q = pr + r * PP + c;
-        q[0] = p0;
-        q[NR * PP] = p1;
-        q[2 * NR * PP] = p2;
-        q[3 * NR * PP] = p3;
-        q[4 * NR * PP] = p4;
+        c2 = c1;
+        c1 = wval[k];
+        if constexpr (FLOW) {
+          fu = wu[k];
+          fv = wv[k];
+        }
       }
     }
     __syncthreads();
-    // ---------------------------------------------------------------- P3
-    // Where the window sums overwrite the products they are made from, every thread first
-    // reads and sums its segments, then all write after a barrier.
-    float hv[C::K3][8];
+    // ------------------------------------------------------------------ P3
+    // The last two warped rows are the next band's first two.
+    if constexpr (BB == 1) {
+      if (more && tid < 2 * WP) w2[tid] = w2[N * WP + tid];
+    }
+    // Items are (segment, channel and row), the row fastest over the lanes.
+    using DS = ConstDiv<5 * NR, C::K3 * NT>;
 #pragma unroll
     for (int k = 0; k < C::K3; ++k) {
       const int i = tid + k * NT;
       if (i < 5 * NR * C::NSEG) {
-        const int seg = (int)((unsigned)i % C::NSEG), rr = (int)((unsigned)i / C::NSEG);   // ch * NR + row
+        const int seg = (int)DS::q((unsigned)i), rr = (int)DS::r((unsigned)i, (unsigned)seg);   // rr = ch * NR + row
         typedef float f4v __attribute__((ext_vector_type(4)));
         const f4v* src = reinterpret_cast<const f4v*>(pr + rr * PP + 8 * seg);
-        float vbuf[4 * C::HL4];
+        // The empty asm takes the four values of a read as one 128-bit register operand, so each
+        // read stays one 128-bit LDS load (the sums below use the values out of order, and the
+        // loads were otherwise split into 32-bit pairs).
+        f4v f[C::HL4];
+        float vbuf[4 * C::HL4], hv[8];
+#pragma unroll
+        for (int q = 0; q < C::HL4; ++q) f[q] = src[q];
 #pragma unroll
         for (int q = 0; q < C::HL4; ++q) {
-          // The empty asm takes the four values as one 128-bit register operand, so each read
-          // stays one 128-bit LDS load (the sums below use the values out of order, and the
-          // loads were otherwise split into 32-bit pairs).
-          f4v f = src[q];
-          asm volatile("" : "+v"(f));
-          vbuf[4 * q] = f.x;
-          vbuf[4 * q + 1] = f.y;
-          vbuf[4 * q + 2] = f.z;
-          vbuf[4 * q + 3] = f.w;
+          asm("" : "+v"(f[q]));
+          vbuf[4 * q] = f[q].x;
+          vbuf[4 * q + 1] = f[q].y;
+          vbuf[4 * q + 2] = f[q].z;
+          vbuf[4 * q + 3] = f[q].w;
         }
         if constexpr (GAUSS) {
 #pragma unroll
@@ -369,7 +419,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
             float s = a.taps[0] * vbuf[j];
 #pragma unroll
             for (int q = 1; q <= 2 * R; ++q) s = fmaf(a.taps[q], vbuf[j + q], s);
-            hv[k][j] = s;
+            hv[j] = s;
           }
         } else if constexpr (2 * R >= 7) {
           // Every window of the segment holds column 2R (the last column of window 0), so
@@ -384,12 +434,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
           sj[7] = suf;
 #pragma unroll
           for (int j = 6; j >= 0; --j) sj[j] = vbuf[j] + sj[j + 1];
-          hv[k][0] = sj[0];
+          hv[0] = sj[0];
           float pre = 0.f;
 #pragma unroll
           for (int j = 1; j < 8; ++j) {
             pre = j == 1 ? vbuf[2 * R + 1] : pre + vbuf[2 * R + j];
-            hv[k][j] = sj[j] + pre;
+            hv[j] = sj[j] + pre;
           }
         } else {
           // r <= 3: direct sums, at most 6 additions per output
@@ -398,32 +448,29 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
             float s = vbuf[j];
 #pragma unroll
             for (int q = 1; q <= 2 * R; ++q) s += vbuf[j + q];
-            hv[k][j] = s;
+            hv[j] = s;
           }
         }
-      }
-    }
-    if constexpr (!kSplit) __syncthreads();
-#pragma unroll
-    for (int k = 0; k < C::K3; ++k) {
-      const int i = tid + k * NT;
-      if (i < 5 * NR * C::NSEG) {
-        const int seg = (int)((unsigned)i % C::NSEG), rr = (int)((unsigned)i / C::NSEG);
-        float4* dst = reinterpret_cast<float4*>(hs + rr * C::TW + 8 * seg);
-        dst[0] = make_float4(hv[k][0], hv[k][1], hv[k][2], hv[k][3]);
-        dst[1] = make_float4(hv[k][4], hv[k][5], hv[k][6], hv[k][7]);
+        float4* dst = reinterpret_cast<float4*>(hs + rr * HP + 8 * seg);
+        dst[0] = make_float4(hv[0], hv[1], hv[2], hv[3]);
+        dst[1] = make_float4(hv[4], hv[5], hv[6], hv[7]);
       }
     }
     __syncthreads();
-    // ---------------------------------------------------------------- P4
+    // ------------------------------------------------------------------ P4
+    FieldRows<MODE, 1> c5[C::K5];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int k = 0; k < C::K5; ++k) centre(c5[k], tb, k);
+    }
     static_assert(!GAUSS || BB == 1, "Gaussian-weighted window: one band per pass");
     if (GAUSS && p4) {
       // Output row r of the band: previous-band rows r+1..N-1 then current rows 0..r, i.e.
       // window offsets 0..N-1 from its top row, weighted by the taps in that order.
-      float* col = hs + vk * N * TW + vc;
+      float* col = hs + vk * N * HP + vc;
       float cur[N];
 #pragma unroll
-      for (int r = 0; r < N; ++r) cur[r] = col[r * TW];
+      for (int r = 0; r < N; ++r) cur[r] = col[r * HP];
 #pragma unroll
       for (int r = 0; r < N; ++r) {
         float s = 0.f;
@@ -431,88 +478,50 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
         for (int m = r + 1; m < N; ++m) s = fmaf(a.taps[m - r - 1], prev[m], s);
 #pragma unroll
         for (int m = 0; m <= r; ++m) s = fmaf(a.taps[N - 1 - r + m], cur[m], s);
-        col[r * TW] = s;
+        col[r * HP] = s;
       }
 #pragma unroll
       for (int r = 0; r < N; ++r) prev[r] = cur[r];
     } else if (p4) {
 #pragma unroll
       for (int bb = 0; bb < BB; ++bb) {
-        float* col = hs + vk * NR * TW + bb * N * TW + vc;
+        float* col = hs + vk * NR * HP + bb * N * HP + vc;
+        // All reads before the first write: one LDS round trip instead of one per few rows.
+        float cur[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) cur[r] = col[r * HP];
+        __builtin_amdgcn_sched_barrier(0);
         // prev[r] <- prev[r] + ... + prev[N-1] (suffix sums of the previous band, in place)
 #pragma unroll
         for (int r = N - 2; r >= 0; --r) prev[r] += prev[r + 1];
         float pre = 0.f;
 #pragma unroll
         for (int r = 0; r < N; ++r) {
-          const float c = col[r * TW];
-          pre = r == 0 ? c : pre + c;
-          col[r * TW] = r + 1 < N ? prev[r + 1] + pre : pre;
-          prev[r] = c;
+          pre = r == 0 ? cur[r] : pre + cur[r];
+          col[r * HP] = r + 1 < N ? prev[r + 1] + pre : pre;
+          prev[r] = cur[r];
         }
       }
     }
     __syncthreads();
-    // ---------------------------------------------------------------- P5
-    if constexpr (kDefer) {
-#pragma unroll
-      for (int k = 0; k < C::K5; ++k) {
-        const int i = min(tid + k * NT, NR * TW - 1);
-        const int gx = INTERIOR ? x0 + (int)((unsigned)i % TW) : min(x0 + (int)((unsigned)i % TW), W - 1);
-        const int gy = min(max(y0 + tb + (int)((unsigned)i / TW) - 2 * R, 0), H - 1);
-        read_flow<MODE>(a, gx, gy, cu[k], cv[k]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < C::K5; ++k) {
-      const int i = tid + k * NT;
-      if (i < NR * TW) {
-        const int r = (int)((unsigned)i / TW), c = (int)((unsigned)i % TW);
-        const int j = tb + r - 2 * R;
-        const int gx = x0 + c, gy = y0 + j;
-        if (j >= 0 && j < TH && (INTERIOR || (gx < W && gy < H))) {
-          const float* s = hs + r * TW + c;
-          float fu, fv;   // field at the output pixel: warped row j + R, column c + R + 1
-          if constexpr (FR) {
-            fu = fru[((j + R) & FMASK) * WP + c + R + 1];
-            fv = frv[((j + R) & FMASK) * WP + c + R + 1];
-          } else {
-            fu = cu[k];
-            fv = cv[k];
-          }
-          float un, vn;
-          solve_update(s[0], s[NR * TW], s[2 * NR * TW], s[3 * NR * TW], s[4 * NR * TW], fu, fv,
-                       un, vn);
-          const unsigned o = rowofs(gy, W, gx);
-          if (pixel_mask && at(a.mask, o) == 0) {   // masked-out pixel: zero flow
-            un = 0.f;
-            vn = 0.f;
-          }
-          at(a.uout, o) = un;
-          at(a.vout, o) = vn;
-          if constexpr (BUB) {
-            if (bub) bcnt += un <= bthr ? 1u : 0u;
-          }
-        }
-      }
-    }
-    // The next pass's P1 writes only warped rows that this pass's P2 finished reading before
-    // the barriers above; its P2 rewrites the product/window-sum buffer after the P1 barrier,
-    // when every thread has finished this pass's P5.
+    // ------------------------------------------------------------------ P5
+    solve(tb, c5);
+    // The next pass's P1 writes warped rows and field rows that this pass's P2 finished reading
+    // before the barriers above; its P3 rewrites the window sums after two more barriers.
   }
   if constexpr (BUB) {
     if (bub) add_count(a.bcount, bcnt);
   }
 }
 
-// True when every warped-frame position of the tile (columns x0-R-1 .. x0+TW+R, rows
-// y0-R-1 .. y0-R+N*nbands) lies inside the image.
-template <int R, int TW>
+// True when every position that the tile samples (columns x0-R-1 .. x0+TW+R, rows y0-R-1 .. the
+// last row of the last pass's threads) lies inside the image.
+template <class C>
 __device__ __forceinline__ bool tile_interior(const IterArgs& a, int nbands, int bx, int y0) {
-  constexpr int N = 2 * R + 1;
-  const int x0 = bx * TW;
-  return x0 - R - 1 >= 0 && x0 + TW + R <= a.W - 1 && y0 - R - 1 >= 0 &&
-         y0 - R + N * nbands <= a.H - 1;
+  constexpr int R = (C::N - 1) / 2;
+  const int x0 = bx * C::TW;
+  const int last = y0 - R - 1 + C::N * nbands - C::NR + C::P1_FIRST + C::G * C::K1 - 1;
+  return x0 - R - 1 >= 0 && x0 + C::TW + R <= a.W - 1 && y0 - R - 1 >= 0 && last <= a.H - 1;
 }
 
 // Masked plans: a tile without an unmasked output pixel (TW columns from x0, TH rows from
@@ -540,8 +549,8 @@ __device__ __forceinline__ int xcd_order(int b, int nblocks) {
   return (b % kXcd) * per + b / kXcd;
 }
 
-template <typename T, int R, int TW, int MODE, bool WIDE, bool LEAN, bool GAUSS, int BB>
-__global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>())) void lk_iter_strip(IterArgs a, int TH,
+template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, int BB>
+__global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd<R, TW, WIDE, BB>())) void lk_iter_strip(IterArgs a, int TH,
                                                                            int nbands, int tiles_x,
                                                                            int ntiles) {
   extern __shared__ float4 sm4[];
@@ -557,14 +566,10 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>())) void lk_iter_st
     }
     pixel_mask = f == 1;
   }
-  constexpr bool kDefer = WIDE || R > 8;
-  constexpr bool kFR = field_ring<MODE, WIDE, LEAN, BB>();
-  if (R <= 8 && tile_interior<R, TW>(a, nbands, bx, y0))
-    strip_tile<T, R, TW, MODE, WIDE, kDefer, true, LEAN, GAUSS, BB, kFR, true>(a, TH, nbands, bx,
-                                                                               y0, pixel_mask, sm4);
+  if (tile_interior<Cfg<R, TW, WIDE, BB>>(a, nbands, bx, y0))
+    strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
   else
-    strip_tile<T, R, TW, MODE, WIDE, kDefer, false, LEAN, GAUSS, BB, kFR, true>(a, TH, nbands, bx,
-                                                                                y0, pixel_mask, sm4);
+    strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
 }
 
 // Batched form: workgroups stride over a work list of tiles of many pairs at the same
@@ -574,8 +579,8 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>())) void lk_iter_st
 // without (2).
 // MASK: launches of batches with masks (the mask code costs the unmasked launches about 5 %
 // more instructions and is compiled out of them).
-template <typename T, int R, int TW, int MODE, bool WIDE, bool LEAN, bool GAUSS, bool MASK>
-__global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>())) void lk_iter_batch(const IterArgs* __restrict__ args,
+template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, bool MASK>
+__global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>()), (waves_per_simd<R, TW, WIDE, 1>())) void lk_iter_batch(const IterArgs* __restrict__ args,
                                                                       const int4* __restrict__ tiles,
                                                                       int ntiles) {
   extern __shared__ float4 sm4[];
@@ -596,31 +601,24 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>())) void lk_iter_bat
         pixel_mask = f == 1;
       }
     }
-    constexpr bool kFR = MODE != kFlowZero;
-    if (R <= 8 && tile_interior<R, TW>(a, nb, w.y, w.z))
-      strip_tile<T, R, TW, MODE, WIDE, true, true, LEAN, GAUSS, 1, kFR>(a, w.w, nb, w.y, w.z,
-                                                                        pixel_mask, sm4);
+    if (tile_interior<C>(a, nb, w.y, w.z))
+      strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     else
-      strip_tile<T, R, TW, MODE, WIDE, true, false, LEAN, GAUSS, 1, kFR>(a, w.w, nb, w.y, w.z,
-                                                                         pixel_mask, sm4);
+      strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     __syncthreads();
   }
 }
 
-// 64-column strips while the LDS footprint stays within 64 KB, else 32-column strips.
-template <int R>
-constexpr int strip_width() {
-  return Cfg<R, 64>::LDS_FLOATS * sizeof(float) <= 65536 ? 64 : 32;
-}
+// Output columns of the strips of variants 0-2.
+constexpr int kStripWidth = 64;
 
 // nb output bands per tile take nb + 1 bands (the first primes the vertical sums), rounded up
 // to whole passes of BB bands (a band past the tile's rows writes nothing).
-template <typename T, int R, int MODE, bool WIDE, bool LEAN, bool GAUSS, int TWV = 0, int BB = 1>
+template <typename T, int R, int MODE, bool WIDE, bool GAUSS, int TWV = 0, int BB = 1>
 hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
-  constexpr int TW = TWV ? TWV : strip_width<R>();
+  constexpr int TW = TWV ? TWV : kStripWidth;
   using C = Cfg<R, TW, WIDE, BB>;
-  constexpr bool kFR = field_ring<MODE, WIDE, LEAN, BB>();
-  constexpr size_t kLds = lds_bytes<R, TW, WIDE, LEAN, BB, kFR>();
+  constexpr size_t kLds = C::LDS_BYTES;
   static_assert(kLds <= 160 * 1024, "LDS footprint above 160 KB");
   const int TH = C::N * nb;
   const int tx = (a.W + TW - 1) / TW, ty = (a.H + TH - 1) / TH;
@@ -630,11 +628,11 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   if constexpr (kLds > 65536) {
     // Opt in to more than 64 KB of dynamic LDS (gfx950 has 160 KB per workgroup), once.
     static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, WIDE, LEAN, GAUSS, BB>),
+        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (opt != hipSuccess) return opt;
   }
-  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, WIDE, LEAN, GAUSS, BB>), dim3(grid),
+  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB>), dim3(grid),
                      dim3(C::NT), kLds, s, a, TH, nbands, tx, ntiles);
   return hipGetLastError();
 }
@@ -642,20 +640,20 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
 template <typename T, int R, int MODE, bool GAUSS>
 hipError_t go_plain_g(const IterArgs& a, int nb, int variant, hipStream_t s) {
   switch (variant) {
-    case kTileNarrow: return go_plain_v<T, R, MODE, false, true, GAUSS>(a, nb, s);
-    case kTileWide: return go_plain_v<T, R, MODE, true, false, GAUSS>(a, nb, s);
-    case kTileWideLean: return go_plain_v<T, R, MODE, true, true, GAUSS>(a, nb, s);
+    case kTileNarrow: return go_plain_v<T, R, MODE, false, GAUSS>(a, nb, s);
+    case kTileWide:
+    case kTileWideLean: return go_plain_v<T, R, MODE, true, GAUSS>(a, nb, s);
   }
   if constexpr (!GAUSS) {   // narrow strips: box window only
     switch (variant) {
-      case kTileWide32: return go_plain_v<T, R, MODE, true, false, false, 32>(a, nb, s);
-      case kTileWide16: return go_plain_v<T, R, MODE, true, false, false, 16>(a, nb, s);
+      case kTileWide32: return go_plain_v<T, R, MODE, true, false, 32>(a, nb, s);
+      case kTileWide16: return go_plain_v<T, R, MODE, true, false, 16>(a, nb, s);
     }
     if constexpr (R <= kMaxPairRadius) {   // two bands per pass
       switch (variant) {
-        case kTileWide32x2: return go_plain_v<T, R, MODE, true, false, false, 32, 2>(a, nb, s);
-        case kTileWide16x2: return go_plain_v<T, R, MODE, true, false, false, 16, 2>(a, nb, s);
-        case kTileLean32x2: return go_plain_v<T, R, MODE, true, true, false, 32, 2>(a, nb, s);
+        case kTileWide32x2:
+        case kTileLean32x2: return go_plain_v<T, R, MODE, true, false, 32, 2>(a, nb, s);
+        case kTileWide16x2: return go_plain_v<T, R, MODE, true, false, 16, 2>(a, nb, s);
       }
     }
   }
@@ -669,43 +667,43 @@ hipError_t go_plain(const IterArgs& a, int nb, int variant, hipStream_t s) {
   return go_plain_g<T, R, MODE, false>(a, nb, variant, s);
 }
 
-template <typename T, int R, int MODE, bool WIDE, bool LEAN, bool GAUSS, bool MASK>
+template <typename T, int R, int MODE, bool WIDE, bool GAUSS, bool MASK>
 hipError_t go_batch_m(const BatchLaunch& b, hipStream_t s) {
-  constexpr int TW = strip_width<R>();
+  constexpr int TW = kStripWidth;
   using C = Cfg<R, TW, WIDE>;
-  constexpr size_t kLds = lds_bytes<R, TW, WIDE, LEAN, 1, MODE != kFlowZero>();
+  constexpr size_t kLds = C::LDS_BYTES;
   if constexpr (kLds > 65536) {
     static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, LEAN, GAUSS, MASK>),
+        reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (opt != hipSuccess) return opt;
   }
   if (b.prime) {
     hipFuncAttributes attr;
     return hipFuncGetAttributes(
-        &attr, reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, LEAN, GAUSS, MASK>));
+        &attr, reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>));
   }
-  hipLaunchKernelGGL((lk_iter_batch<T, R, TW, MODE, WIDE, LEAN, GAUSS, MASK>), dim3(b.grid),
+  hipLaunchKernelGGL((lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>), dim3(b.grid),
                      dim3(C::NT), kLds, s, b.args, b.tiles, b.ntiles);
   return hipGetLastError();
 }
 
-template <typename T, int R, int MODE, bool WIDE, bool LEAN, bool GAUSS>
+template <typename T, int R, int MODE, bool WIDE, bool GAUSS>
 hipError_t go_batch_v(const BatchLaunch& b, hipStream_t s) {
-  return b.masked ? go_batch_m<T, R, MODE, WIDE, LEAN, GAUSS, true>(b, s)
-                  : go_batch_m<T, R, MODE, WIDE, LEAN, GAUSS, false>(b, s);
+  return b.masked ? go_batch_m<T, R, MODE, WIDE, GAUSS, true>(b, s)
+                  : go_batch_m<T, R, MODE, WIDE, GAUSS, false>(b, s);
 }
 
 // b.variant: OF_TILE_NARROW, _WIDE or _WIDE_LEAN, plus kTileGauss for the Gaussian window.
 template <typename T, int R, int MODE>
 hipError_t go_batch(const BatchLaunch& b, hipStream_t s) {
   switch (b.variant) {
-    case kTileNarrow: return go_batch_v<T, R, MODE, false, true, false>(b, s);
-    case kTileWide: return go_batch_v<T, R, MODE, true, false, false>(b, s);
-    case kTileWideLean: return go_batch_v<T, R, MODE, true, true, false>(b, s);
-    case kTileNarrow | kTileGauss: return go_batch_v<T, R, MODE, false, true, true>(b, s);
-    case kTileWide | kTileGauss: return go_batch_v<T, R, MODE, true, false, true>(b, s);
-    case kTileWideLean | kTileGauss: return go_batch_v<T, R, MODE, true, true, true>(b, s);
+    case kTileNarrow: return go_batch_v<T, R, MODE, false, false>(b, s);
+    case kTileWide:
+    case kTileWideLean: return go_batch_v<T, R, MODE, true, false>(b, s);
+    case kTileNarrow | kTileGauss: return go_batch_v<T, R, MODE, false, true>(b, s);
+    case kTileWide | kTileGauss:
+    case kTileWideLean | kTileGauss: return go_batch_v<T, R, MODE, true, true>(b, s);
   }
   return hipErrorInvalidValue;
 }
@@ -725,25 +723,12 @@ hipError_t go_r(const IterArgs* a, const BatchLaunch* b, int mode, int nb, int v
 }
 
 // Plain launch (a != nullptr; tile height N*nb, tile variant `variant`) or batched launch
-// (b != nullptr; its own variant).
-template <typename T>
+// (b != nullptr; its own variant) of a radius in [LO, HI].
+template <typename T, int LO, int HI>
 hipError_t launch_iter_t(const IterArgs* a, const BatchLaunch* b, int R, int mode, int nb,
                          int variant, hipStream_t s) {
-  switch (R) {
-    case 0: return go_r<T, 0>(a, b, mode, nb, variant, s);
-    case 1: return go_r<T, 1>(a, b, mode, nb, variant, s);
-    case 2: return go_r<T, 2>(a, b, mode, nb, variant, s);
-    case 3: return go_r<T, 3>(a, b, mode, nb, variant, s);
-    case 4: return go_r<T, 4>(a, b, mode, nb, variant, s);
-    case 5: return go_r<T, 5>(a, b, mode, nb, variant, s);
-    case 6: return go_r<T, 6>(a, b, mode, nb, variant, s);
-    case 7: return go_r<T, 7>(a, b, mode, nb, variant, s);
-    case 8: return go_r<T, 8>(a, b, mode, nb, variant, s);
-    case 9: return go_r<T, 9>(a, b, mode, nb, variant, s);
-    case 10: return go_r<T, 10>(a, b, mode, nb, variant, s);
-    case 11: return go_r<T, 11>(a, b, mode, nb, variant, s);
-    case 12: return go_r<T, 12>(a, b, mode, nb, variant, s);
-  }
+  if (R == LO) return go_r<T, LO>(a, b, mode, nb, variant, s);
+  if constexpr (LO < HI) return launch_iter_t<T, LO + 1, HI>(a, b, R, mode, nb, variant, s);
   return hipErrorInvalidValue;
 }
 
