@@ -83,11 +83,9 @@ typedef enum {
                                           kernels one by one) */
 
 /* Tile variants of the fused iteration kernel (launch configuration; results do not depend
- * on them).  NARROW: 5 threads per output column.  WIDE: 10 threads per output column with
- * per-thread item indices held in registers (shortest dependent path per band, for launches
- * of about one tile per CU).  WIDE_LEAN: 10 threads per output column, indices recomputed
- * every band (fewer live registers, so two workgroups share a CU, for launches of many
- * tiles). */
+ * on them).  NARROW: strips of 64 output columns, 5 threads per output column.  WIDE: the same
+ * strips with about 12 threads per output column (two workgroups share a CU up to r = 8).
+ * WIDE_LEAN: the same kernel as WIDE. */
 #define OF_TILE_NARROW 0
 #define OF_TILE_WIDE 1
 #define OF_TILE_WIDE_LEAN 2
@@ -96,14 +94,12 @@ typedef enum {
  * shorter path per band. */
 #define OF_TILE_WIDE32 3
 #define OF_TILE_WIDE16 4
-/* Plans with the box window and r <= 8 only: WIDE32 / WIDE16 with two bands per pass (20
- * threads per output column): a tile's priming band and first output band (a tile of one
- * output band is exactly these two) take one dependent path through the kernel instead of
- * two, for levels of about one tile per CU. */
+/* Plans with the box window and r <= 8 only: WIDE32 / WIDE16 with two bands per pass: a tile's
+ * priming band and first output band (a tile of one output band is exactly these two) take one
+ * dependent path through the kernel instead of two, for levels of about one tile per CU.
+ * LEAN32X2: the same kernel as WIDE32X2. */
 #define OF_TILE_WIDE32X2 5
 #define OF_TILE_WIDE16X2 6
-/* WIDE32X2 with the item indices recomputed every pass (as WIDE_LEAN): 60-80 instead of
- * 96-134 VGPRs, so two or three workgroups share a CU, for levels with more tiles than CUs. */
 #define OF_TILE_LEAN32X2 7
 
 #define OF_MAX_LEVELS 12
@@ -189,20 +185,18 @@ OF_API of_status of_plan_set_mask(of_plan* plan, const uint8_t* mask, void* stre
 OF_API int of_levels_for_displacement(float dmax, int H, int W);
 
 /* Per-level launch configuration of a plan: bands[l] = tile height of the iteration kernel
- * in bands of 2r+1 rows (1..64), variant[l] = OF_TILE_* (defaults: 4 bands for levels of 2^19
- * pixels and more, else 1; levels of under 384 tiles of 64 columns at that height take WIDE32
- * with 4 bands, WIDE16X2 (under 128 tiles) or LEAN32X2 with 1 band (WIDE32 above r = 8, WIDE
- * with OF_FLAG_GAUSSIAN_WINDOW), larger ones WIDE_LEAN;
+ * in bands of 2r+1 rows (1..64), variant[l] = OF_TILE_* (defaults: the variant and height of
+ * least estimated time for the level's size and radius among WIDE and, with the box window,
+ * WIDE32 for r <= 3 and r > 8, WIDE16 for r > 8, WIDE32X2 and WIDE16X2 for r <= 8;
  * WIDE32, WIDE16 and the X2 variants are not available with OF_FLAG_GAUSSIAN_WINDOW, the X2
- * variants not above r = 8).  Arrays of `levels` entries.  set_config drops the plan's captured graphs; OF_EINVAL for values out
- * of range.  Results do not depend on the configuration. */
+ * variants not above r = 8).  Arrays of `levels` entries.  set_config drops the plan's captured
+ * graphs; OF_EINVAL for values out of range.  Results do not depend on the configuration. */
 OF_API of_status of_plan_get_config(const of_plan* plan, int* bands, int* variant);
 OF_API of_status of_plan_set_config(of_plan* plan, const int* bands, const int* variant);
 
 /* Autotuner: for each level in turn, times that level's iteration launches for bands in
- * {1,2,3,4,8} x the tile variants the plan allows (eight with the box window and r <= 8, five
- * with the box window above, three with the Gaussian window)
- * on the given buffers (reps timed runs after one warm-up) and keeps the fastest.
+ * {1,2,3,4,6,8,12,16} x the kernels the plan allows (six with the box window and r <= 8, four
+ * with the box window above, two with the Gaussian window) on the given buffers (reps timed runs after one warm-up) and keeps the fastest.
  * Synchronises `stream`; writes u, v. */
 OF_API of_status of_plan_autotune(of_plan* plan, const void* I1, const void* I2, float* u,
                                   float* v, void* stream, int reps);
@@ -282,16 +276,16 @@ OF_API of_status of_batch_compute(of_batch* b, const void* const* I1, const void
 /* Per-level launch configuration: bands[l] = tile height in bands of 2r+1 rows (1..64),
  * grid[l] = workgroups of the iteration launches (0 = one per tile, else a persistent grid
  * striding over the work list), variant[l] = OF_TILE_NARROW, _WIDE or _WIDE_LEAN, or -1 for
- * the default (WIDE for launches of under 384 tiles, else WIDE_LEAN).  Arrays of `levels` entries; `variant` may
- * be NULL (get: not returned; set: -1 for every level).  set_config rebuilds the work lists
+ * the default (WIDE).  The default heights are those of least estimated time for the batch's
+ * sizes.  Arrays of `levels` entries; `variant` may be NULL (get: not returned; set: -1 for every level).  set_config rebuilds the work lists
  * and drops captured graphs. */
 OF_API of_status of_batch_get_config(const of_batch* b, int* bands, int* grid, int* variant);
 OF_API of_status of_batch_set_config(of_batch* b, const int* bands, const int* grid,
                                      const int* variant);
 
 /* Autotuner: for each level in turn, times that level's iteration launches for every
- * candidate (bands in {1,2,4,8}, grid in {one per tile, 256, 512, 1024, 2048}, the three
- * tile variants) on the given buffers (reps timed runs after one warm-up) and keeps the
+ * candidate (bands in {1,2,4,8,16,32}, grid in {one per tile, 256, 512, 1024, 2048}, NARROW and
+ * WIDE tiles) on the given buffers (reps timed runs after one warm-up) and keeps the
  * fastest.  Synchronises `stream`.  The chosen configuration is read back with
  * of_batch_get_config. */
 OF_API of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* const* I2,

@@ -117,12 +117,11 @@ bool check_batch(int n, const int* H, const int* W, int levels, int radius, int 
 }
 
 int default_batch_bands(const of_batch* b, int l) {
-  long long px = 0;
-  for (int i = 0; i < b->n; ++i) px += (long long)b->g[i].H[l] * b->g[i].W[l];
-  // Many pairs fill the device even with tall tiles, which cut the vertical halo.
-  if (px >= (24ll << 20)) return 4;
-  if (px >= (4ll << 20)) return 2;
-  return 1;
+  std::vector<PlaneSize> s;
+  for (const Geometry& g : b->g) s.push_back({g.H[l], g.W[l]});
+  int cand[32];
+  for (int i = 0; i < 32; ++i) cand[i] = i + 1;
+  return best_bands(s.data(), b->n, b->R, kTileWide, cand, 32);
 }
 
 // Work items one pair's level can need at any tile height: the one-band tiles, or at taller
@@ -334,7 +333,7 @@ hipError_t enqueue_batch(of_batch* b, char* blk, float* const* u, float* const* 
       const int nzero = (l == 0 && k == K - 1) ? b->ntiles[l] - b->nactive[l] : 0;
       bl.grid = b->cfg[l].grid > 0 ? std::min(b->cfg[l].grid, bl.ntiles) : bl.ntiles;
       bl.grid = (bl.grid + 7) / 8 * 8;
-      bl.variant = b->cfg[l].variant >= 0 ? b->cfg[l].variant : default_tile_variant(b->ntiles[l]);
+      bl.variant = b->cfg[l].variant >= 0 ? b->cfg[l].variant : kTileWide;
       if (b->flags & OF_FLAG_GAUSSIAN_WINDOW) bl.variant |= kTileGauss;
       // Only tiles that hold masked and unmasked pixels need the masked kernel.
       bl.masked = b->maskbuf != nullptr && b->partial[l];
@@ -715,9 +714,9 @@ of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* cons
   const int was_mode = b->timer.mode;
   b->timer.on = true;
   b->timer.mode = OF_TIMING_LAUNCH;
-  static const int kBands[] = {1, 2, 4, 8, 16};
+  static const int kBands[] = {1, 2, 4, 8, 16, 32};
   static const int kGrid[] = {0, 256, 512, 1024, 2048};
-  static const int kVariant[] = {kTileNarrow, kTileWide, kTileWideLean};
+  static const int kVariant[] = {kTileNarrow, kTileWide};
   hipError_t e = hipSuccess;
   // Coordinate descent, one level at a time: the iteration time of that level only.
   for (int l = 0; l < b->L && e == hipSuccess; ++l) {

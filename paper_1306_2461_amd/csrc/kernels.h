@@ -49,19 +49,15 @@ hipError_t launch_reduce(Elem tin, Elem tout, const void* in1, const void* in2, 
                          void* out1, void* out2, int Ho, int Wo, hipStream_t s);
 
 // Tile variants of the iteration kernel:
-//   narrow     5 threads per output column, item indices recomputed every band;
-//   wide       10 threads per output column, item indices kept in registers (shortest
-//              dependent path per band: launches with about one tile per CU);
-//   wide lean  10 threads per output column, indices recomputed every band (fewer live
-//              registers, so more resident workgroups: launches with many tiles).
+//   narrow     64-column strips, 5 threads per output column;
+//   wide       64-column strips, about 12 threads per output column;
 //   wide 32 /  the wide variant on strips of 32 or 16 output columns (plain launches of the
-//   wide 16    box window): small levels spread over more CUs, fewer waves per SIMD per tile,
-//              hence a shorter path per band where a level has fewer tiles than CUs.
-//   wide 32x2 / the same strips with two bands per pass and 20 threads per output column
-//   wide 16x2   (plain launches of the box window, r <= kMaxPairRadius): a tile of one output
-//              band runs its priming band and its output band together, one dependent path.
-//   lean 32x2   wide 32x2 with the item indices recomputed every pass (as wide lean): fewer
-//              live registers, so several workgroups share a CU (levels with more tiles).
+//   wide 16    box window): small levels spread over more CUs, hence a shorter path per band
+//              where a level has fewer tiles than CUs.
+//   wide 32x2 / the same strips with two bands per pass (plain launches of the box window,
+//   wide 16x2   r <= kMaxPairRadius): a tile of one output band runs its priming band and its
+//              output band together, one dependent path.
+//   wide lean, lean 32x2: the kernels of wide and wide 32x2 (kept as configuration values).
 enum TileVariant : int { kTileNarrow = 0, kTileWide = 1, kTileWideLean = 2, kTileWide32 = 3,
                          kTileWide16 = 4, kTileWide32x2 = 5, kTileWide16x2 = 6, kTileLean32x2 = 7 };
 constexpr int kTileVariants = 8;
@@ -87,6 +83,12 @@ struct BatchLaunch {
   bool prime = false;
 };
 
+// Workgroup of a tile variant at radius R: output columns, bands per pass, threads, workgroups
+// that share a CU.
+struct TileShape {
+  int tw, bb, threads, per_cu;
+};
+TileShape tile_shape(int variant, int R);
 // Strip width (output columns per tile) of the iteration kernel for radius R (variants 0-2).
 int strip_width_for(int R);
 // Strip width of a plain launch's tile variant.

@@ -141,8 +141,15 @@ std::vector<uint8_t> tile_flags(const uint8_t* mask, int H, int W, int TW, int T
 // the tile's first to its last band that holds an unmasked pixel; the band boundaries stay
 // where the tile's are, so the window sums round as in the uncut tile.
 void band_cut(const uint8_t* m, int W, int c0, int c1, int y0, int e, int N, int& ty0, int& th);
-int default_bands(int H, int W, int R);
-int default_tile_variant(long long ntiles);
+// Size of one pair's plane at a level.
+struct PlaneSize {
+  int H, W;
+};
+// Estimated time of one iteration launch over n planes with tile variant `variant` and tiles of nb
+// bands, in units of one band of a lone wide tile (see the definition).
+double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb);
+// The tile height of least estimated cost among `cand`.
+int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, int ncand);
 bool check_params(int H, int W, int levels, int radius, int iters, unsigned flags);
 Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned flags);
 hipError_t enqueue_pair(const Geometry& g, char* ws, const void* I1, const void* I2, float* u,

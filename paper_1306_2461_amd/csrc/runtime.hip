@@ -37,20 +37,56 @@ bool check_params(int H, int W, int levels, int radius, int iters, unsigned flag
   return true;
 }
 
-// Tile height (in bands of 2R+1 rows) of a plan's iteration kernel for one level: planes of
-// 2^19 pixels and more take four bands (the vertical halo and the priming band amortised over
-// more rows; fastest measured at 1024^2 and 2048^2), smaller ones one band (more workgroups,
-// and the two-bands-per-pass variants run a one-band tile as a single trip).
-int default_bands(int H, int W, int R) {
-  const long long px = (long long)H * W;
-  (void)R;
-  return px >= (1 << 19) ? 4 : 1;
+// A launch's time by its tiles, fitted to event timings of every variant and tile height at r = 2, 4,
+// 8, 10 on levels of 200^2 .. 2048^2 and on 16 pairs of 1024^2 (it ranks the heights as measured, or
+// picks one within a few per cent).  A tile of nb output bands walks nb + 1 (the first primes the
+// vertical sums) and costs a quarter band to start.  A band takes one unit on a CU of its own; k
+// workgroups of t threads sharing the CU slow each other to 1 + 0.6 (k-1) t/768 (r = 8: 2.03 us
+// alone, 3.3 us in twos).  Tiles beyond what the 256 CUs hold at once run in further rounds; many
+// rounds even out, and only the total and a part of a last tile count.  Examples (r = 8, measured /
+// model): 2048^2 at 8 bands 32.9 us / 16.8, 4 bands 36.3 / 18.8, 16 bands 42.1 / 19.3; 1024^2 at 2
+// bands 14.4 / 7.2, 3 bands 16.6 / 8.8, 4 bands 15.0 / 7.3; 16 x 1024^2 at 31 bands 123, 16 bands 123,
+// 8 bands 128, 4 bands 149, 2 bands 168 us.
+double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb) {
+  constexpr int kCus = 256;
+  const TileShape sh = tile_shape(variant, R);
+  const int N = 2 * R + 1;
+  // cost of the launch and a tile's ends, and of a band, by strip width and bands per pass
+  const double base = sh.bb == 2 || sh.tw == 32 ? 1.5 : (sh.tw == 16 ? 1.0 : 2.0);
+  const double band = sh.bb == 2 ? (sh.tw == 16 ? 0.58 : 0.75) : (sh.tw == 16 ? 0.85 : (sh.tw == 32 ? 0.9 : 1.0));
+  long long tiles = 0;
+  double work = 0, tall = 0;
+  for (int i = 0; i < n; ++i) {
+    const int bands = (s[i].H + N - 1) / N, h = std::min(nb, bands);
+    const long long tx = (s[i].W + sh.tw - 1) / sh.tw, ty = (bands + nb - 1) / nb;
+    tiles += tx * ty;
+    work += tx * (bands + 1.25 * ty);
+    tall = std::max(tall, (h + 1 + sh.bb - 1) / sh.bb * sh.bb + 0.25);
+  }
+  auto shared = [&](long long t) {   // slow-down of t tiles spread over the CUs
+    return 1.0 + 0.6 * ((t + kCus - 1) / kCus - 1) * sh.threads / 768.0;
+  };
+  const long long slots = (long long)kCus * sh.per_cu, full = tiles / slots, rest = tiles % slots;
+  double t;
+  if (full < 3)
+    t = full * shared(slots) * tall + (rest ? shared(rest) * tall : 0.0);
+  else
+    t = shared(slots) * (work / slots + (rest ? 0.25 * tall : 0.0));
+  return base + band * t;
 }
 
-// Launches of about one tile per CU are latency bound and take the wide variant (shortest
-// dependent path per band); launches with more tiles take the wide lean variant, whose lower
-// register count lets two workgroups share a CU.
-int default_tile_variant(long long ntiles) { return ntiles >= 384 ? kTileWideLean : kTileWide; }
+int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, int ncand) {
+  int best = cand[0];
+  double cost = 1e300;
+  for (int i = 0; i < ncand; ++i) {
+    const double c = iter_cost(s, n, R, variant, cand[i]);
+    if (c < cost) {
+      cost = c;
+      best = cand[i];
+    }
+  }
+  return best;
+}
 
 Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned flags) {
   Geometry g{};
@@ -65,25 +101,28 @@ Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned
     g.W[l] = (g.W[l - 1] + 1) / 2;
   }
   for (int l = 0; l < levels; ++l) {
-    g.nb[l] = default_bands(g.H[l], g.W[l], radius);
-    {
-      // Variant by the level's tile count on 64-column strips at that height.  Levels of many
-      // tiles, and the Gaussian-weighted window, take the batch default (wide lean, or wide
-      // below 384 tiles).  With the box window (fastest measured at 1024^2 and 2048^2) levels
-      // of about one tile per CU take 32-column strips: with one-band tiles two bands per pass
-      // (16-column strips below 128 tiles; indices recomputed per pass otherwise), r <= 8;
-      // with taller tiles, or above r = 8, one band per pass.
-      const long long tx = (g.W[l] + strip_width_for(radius) - 1) / strip_width_for(radius);
-      const long long th = (long long)(2 * radius + 1) * g.nb[l];
-      const long long nt = tx * ((g.H[l] + th - 1) / th);
-      const int v = default_tile_variant(nt);
-      g.variant[l] = v;
-      if (v == kTileWide && !(flags & OF_FLAG_GAUSSIAN_WINDOW)) {
-        if (g.nb[l] > 1 || radius > kMaxPairRadius)
-          g.variant[l] = kTileWide32;
-        else
-          g.variant[l] = nt < 128 ? kTileWide16x2 : kTileLean32x2;
+    // Variant and tile height of least estimated cost: 64-column strips, with the box window also
+    // strips of 32 columns (r <= 3, whose bands are short, and r > 8, which has no two-band
+    // passes) or 16 (r > 8) and two bands per pass (r <= 8; whole passes: an odd height).
+    const bool box = !(flags & OF_FLAG_GAUSSIAN_WINDOW);
+    const PlaneSize s = {g.H[l], g.W[l]};
+    double cost = 1e300;
+    auto consider = [&](int variant, int step) {
+      for (int nb = 1; nb <= 32; nb += step) {
+        const double c = iter_cost(&s, 1, radius, variant, nb);
+        if (c < cost) {
+          cost = c;
+          g.variant[l] = variant;
+          g.nb[l] = nb;
+        }
       }
+    };
+    consider(kTileWide, 1);
+    if (box && (radius <= 3 || radius > kMaxPairRadius)) consider(kTileWide32, 1);
+    if (box && radius > kMaxPairRadius) consider(kTileWide16, 1);
+    if (box && radius <= kMaxPairRadius) {
+      consider(kTileWide32x2, 2);
+      consider(kTileWide16x2, 2);
     }
   }
   g.ein = (flags & OF_FLAG_INPUT_F32) ? Elem::F32 : Elem::U8;
@@ -707,7 +746,7 @@ of_status of_plan_autotune(of_plan* p, const void* I1, const void* I2, float* u,
   const int was_mode = p->timer.mode;
   p->timer.on = true;
   p->timer.mode = OF_TIMING_LAUNCH;
-  static const int kBands[] = {1, 2, 3, 4, 8};
+  static const int kBands[] = {1, 2, 3, 4, 6, 8, 12, 16};
   hipError_t e = hipSuccess;
   for (int l = 0; l < g.L && e == hipSuccess && g.K > 0; ++l) {
     double best = 1e30;
@@ -717,6 +756,7 @@ of_status of_plan_autotune(of_plan* p, const void* I1, const void* I2, float* u,
       if (nb > 1 && (2 * g.R + 1) * nb > 2 * g.H[l]) continue;
       for (int w = kTileNarrow; w < kTileVariants; ++w) {
         if (!tile_variant_valid(w, g.R, g.flags & OF_FLAG_GAUSSIAN_WINDOW)) continue;
+        if (w == kTileWideLean || w == kTileLean32x2) continue;   // the same kernels as wide, wide 32x2
         g.nb[l] = nb;
         g.variant[l] = w;
         if (g.mask[l]) e = upload_tile_flags(p, l);

@@ -49,6 +49,10 @@ of_status hip_fail(const char* what, hipError_t e) {
 
 constexpr int kRing = OF_SERVER_RING;   // staging slots per server (pushes in flight at once)
 
+// Tile heights (in bands) a push may choose, each with tile flags of its own in a masked session.
+constexpr int kPushBands[] = {1, 2, 4, 8, 16};
+constexpr int kPushHeights = sizeof(kPushBands) / sizeof(int);
+
 }  // namespace
 
 struct of_server;
@@ -72,7 +76,7 @@ struct of_session {
   // kept on the host, where the push work lists are built.
   uint8_t* maskbuf = nullptr;
   size_t mask_off[OF_MAX_LEVELS] = {};
-  size_t flag_off[3][OF_MAX_LEVELS] = {};
+  size_t flag_off[kPushHeights][OF_MAX_LEVELS] = {};
   size_t plane_off[OF_MAX_LEVELS] = {};
   std::vector<uint8_t> hflags;
   std::vector<int2> hcut;
@@ -100,7 +104,7 @@ struct of_server {
 namespace {
 
 // Loads every iteration kernel a push of this server may launch (each level's frame type and
-// field source, the wide and wide lean tiles, with or without masks) on the current device, so
+// field source, with or without masks) on the current device, so
 // that no push pays a kernel's first-launch code load (about 10 ms measured on a request).
 hipError_t prime_push_kernels(const of_server* s, bool masked) {
   const int side = 1 << (s->L - 1);
@@ -109,13 +113,12 @@ hipError_t prime_push_kernels(const of_server* s, bool masked) {
   bl.prime = true;
   bl.masked = masked;
   for (int l = 0; l < s->L; ++l)
-    for (int k = 0; k < std::min(s->K, 2); ++k)
-      for (int v : {(int)kTileWide, (int)kTileWideLean}) {
-        bl.variant = v | ((s->flags & OF_FLAG_GAUSSIAN_WINDOW) ? kTileGauss : 0);
-        const int mode = k > 0 ? kFlowSame : (l == s->L - 1 ? kFlowZero : kFlowCoarse);
-        const hipError_t e = launch_iter_batch(g.elem(l), bl, s->R, mode, nullptr);
-        if (e != hipSuccess) return e;
-      }
+    for (int k = 0; k < std::min(s->K, 2); ++k) {
+      bl.variant = kTileWide | ((s->flags & OF_FLAG_GAUSSIAN_WINDOW) ? kTileGauss : 0);
+      const int mode = k > 0 ? kFlowSame : (l == s->L - 1 ? kFlowZero : kFlowCoarse);
+      const hipError_t e = launch_iter_batch(g.elem(l), bl, s->R, mode, nullptr);
+      if (e != hipSuccess) return e;
+    }
   return masked ? prime_zero_tiles() : hipSuccess;
 }
 
@@ -170,9 +173,6 @@ void pack(const Push& p, char* dst) {
   for (size_t i = 0; i < p.tiles.size(); ++i)
     memcpy(dst + p.off_tiles[i], p.tiles[i].data(), p.tiles[i].size() * sizeof(int4));
 }
-
-// Tile height (bands) of a push level: taller tiles when many pixels fill the device.
-int push_bands(long long px) { return px >= (24ll << 20) ? 4 : (px >= (4ll << 20) ? 2 : 1); }
 
 // Upper bound of the staging bytes of a push of every session in `ss` (all flowing, one-band
 // tiles, every array padded to 256 bytes): a push of any subset packs into fewer bytes.
@@ -232,9 +232,11 @@ bool check_server_flags(unsigned flags) {
   return true;
 }
 
-// Tile heights (in bands) a push may choose (push_bands) and their slot in a session's flags.
-constexpr int kPushBands[3] = {1, 2, 4};
-int band_slot(int nb) { return nb == 1 ? 0 : (nb == 2 ? 1 : 2); }
+int band_slot(int nb) {
+  int i = 0;
+  while (kPushBands[i] != nb) ++i;
+  return i;
+}
 
 // Servers behind of_session_create, one per (device, levels, radius, iters, flags).
 std::mutex g_hidden_mu;
@@ -418,9 +420,9 @@ of_status of_server_push(of_server* s, of_session* const* ss, int n, const void*
   p.partial.assign(L, 0);
   int level_bands[OF_MAX_LEVELS];
   for (int l = L - 1; l >= 0; --l) {
-    long long px = 0;
-    for (int i : flowing) px += (long long)ss[i]->g.H[l] * ss[i]->g.W[l];
-    level_bands[l] = push_bands(px);
+    std::vector<PlaneSize> sizes;
+    for (int i : flowing) sizes.push_back({ss[i]->g.H[l], ss[i]->g.W[l]});
+    level_bands[l] = best_bands(sizes.data(), (int)sizes.size(), R, kTileWide, kPushBands, kPushHeights);
     const int TH = N * level_bands[l];
     std::vector<int4> off;   // all-masked tiles, after the active ones
     for (int q = 0; q < (int)flowing.size(); ++q) {
@@ -534,7 +536,7 @@ of_status of_server_push(of_server* s, of_session* const* ss, int n, const void*
       bl.ntiles = p.nactive[l];
       const int nzero = (l == 0 && k == K - 1) ? (int)p.tiles[l].size() - p.nactive[l] : 0;
       bl.grid = (bl.ntiles + 7) / 8 * 8;
-      bl.variant = default_tile_variant((int)p.tiles[l].size());
+      bl.variant = kTileWide;
       if (s->flags & OF_FLAG_GAUSSIAN_WINDOW) bl.variant |= kTileGauss;
       bl.masked = p.partial[l];   // only tiles with masked and unmasked pixels need the mask
       const int mode = k > 0 ? kFlowSame : (l == L - 1 ? kFlowZero : kFlowCoarse);
@@ -587,7 +589,7 @@ of_status of_session_set_mask(of_session* ss, const uint8_t* mask, void* stream)
   for (int l = 0; l < L; ++l) {
     ss->mask_off[l] = mt;
     mt += align256((size_t)g.H[l] * g.W[l]);
-    for (int b = 0; b < 3; ++b) {
+    for (int b = 0; b < kPushHeights; ++b) {
       ss->flag_off[b][l] = ft;
       const int TH = N * kPushBands[b];
       ft += (size_t)((g.W[l] + TW - 1) / TW) * ((g.H[l] + TH - 1) / TH);
@@ -615,7 +617,7 @@ of_status of_session_set_mask(of_session* ss, const uint8_t* mask, void* stream)
   for (int l = 0; l < L && e == hipSuccess; ++l) {
     std::vector<uint8_t> hm((size_t)g.H[l] * g.W[l]);
     e = hipMemcpy(hm.data(), mb + ss->mask_off[l], hm.size(), hipMemcpyDeviceToHost);
-    for (int b = 0; b < 3 && e == hipSuccess; ++b) {
+    for (int b = 0; b < kPushHeights && e == hipSuccess; ++b) {
       const int TH = N * kPushBands[b];
       const std::vector<uint8_t> f = tile_flags(hm.data(), g.H[l], g.W[l], TW, TH);
       const size_t o = ss->flag_off[b][l];
