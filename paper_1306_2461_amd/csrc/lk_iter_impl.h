@@ -316,7 +316,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     __syncthreads();
     // ------------------------------------------------------------------ P3
     // The last two warped rows are the next band's first two.
-    if constexpr (BB == 1) {
+    if constexpr (BB == 1 && R == 0) {   // the row moved first is the next one's place
+      if (more && tid < WP) {
+        w2[tid] = w2[WP + tid];
+        w2[WP + tid] = w2[2 * WP + tid];
+      }
+    } else if constexpr (BB == 1) {
       if (more && tid < 2 * WP) w2[tid] = w2[N * WP + tid];
     }
     // Items are (segment, channel and row), the row fastest over the lanes.
