@@ -54,14 +54,15 @@ hipError_t launch_reduce(Elem tin, Elem tout, const void* in1, const void* in2, 
 //   wide 32 /  the wide variant on strips of 32 or 16 output columns (plain launches of the
 //   wide 16    box window): small levels spread over more CUs, hence a shorter path per band
 //              where a level has fewer tiles than CUs.
-//   wide 32x2 / the same strips with two bands per pass (plain launches of the box window,
-//   wide 16x2   r <= kMaxPairRadius): a tile of one output band runs its priming band and its
+//   wide 32x2 / the same strips with two bands per pass (plain launches, r <= kMaxPairRadius; for
+//   wide 16x2   the Gaussian window chosen by the host for tiles of one output band): a tile of one output band runs its priming band and its
 //              output band together, one dependent path.
 //   wide lean, lean 32x2: the kernels of wide and wide 32x2 (kept as configuration values).
 enum TileVariant : int { kTileNarrow = 0, kTileWide = 1, kTileWideLean = 2, kTileWide32 = 3,
                          kTileWide16 = 4, kTileWide32x2 = 5, kTileWide16x2 = 6, kTileLean32x2 = 7 };
 constexpr int kTileVariants = 8;
-// Largest window radius of the two-bands-per-pass variants (their LDS stays within 64 KB).
+// Largest window radius of the two-bands-per-pass variants (two workgroups share a CU's
+// LDS).
 constexpr int kMaxPairRadius = 8;
 // Added to a plain launch's variant: Gaussian-weighted window sums (taps in IterArgs::taps).
 constexpr int kTileGauss = 16;

@@ -19,9 +19,14 @@
 //           band up to row i (fixed order; bands sit on a global grid of period N), or the
 //           direct weighted sum over the same rows for the Gaussian-weighted window;
 //       P5  per-pixel 2x2 solve and update for the band's output rows.
+//           The Gaussian sums are 2r+1 multiply-adds each and bound their P4: the rows of a column
+//           are split over two threads (over all threads in two-band passes), results go where the
+//           products were, and a tile's first band forms only the row that it outputs.  r = 8,
+//           per iteration: 1024^2 21.7 -> 20.5 us, 128^2 10.4 -> 9.5 us in 64-column strips and
+//           5.7 us in two-band passes on 16 columns (512^2, 32 columns: 11.9 -> 9.9 us);
 //   The window sums therefore do not depend on how the image is cut into tiles.
 //   * two-bands-per-pass variants run the five phases once over two bands' rows, so a one-band
-//     tile (output band plus priming band) is one trip.
+//     tile (output band plus priming band) is one trip (Gaussian window: one-band tiles only).
 //
 // What bounds it: vector instructions and the waits between the five phases; HBM is at about
 // half of what a copy reaches.  Two workgroups per CU hide each other's barriers and load rounds,
@@ -137,8 +142,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   using S = Sample<T>;
 
   // P4 ownership: channel and column of this thread (the first 5*TW threads).
-  const int vk = tid / TW, vc = tid - vk * TW;
-  const bool p4 = vk < 5;
+  // The Gaussian-weighted window's takes the threads past those too: the first 5*TW threads one
+  // part of the rows, the next 5*TW the following part, and so on.
+  constexpr int P4S = !GAUSS ? 1 : (BB == 2 ? NT / (5 * TW) : (NT >= 10 * TW ? 2 : 1));
+  const int vq = GAUSS ? tid / (5 * TW) : 0;
+  const int vk = tid / TW - 5 * vq, vc = tid % TW;
+  const bool p4 = GAUSS ? vq < P4S : vk < 5;
   // P5 ownership: output column and row of a round (the row is uniform over a wave on
   // 64-column strips).
   const int oc = tid % TW, orow = TW == 64 ? __builtin_amdgcn_readfirstlane(tid / TW) : tid / TW;
@@ -185,6 +194,9 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   // the field c at this thread's output pixels.  Lanes without an output pixel store past the
   // plane (dropped), so that the number of stores in flight is known where the samples issued
   // before them are waited for.
+  // (The Gaussian-weighted window's sums replace the products, whose last readers P3 were.)
+  const float* win = GAUSS ? pr : hs;
+  constexpr int VP = GAUSS ? PP : HP;
   auto solve = [&](int tb, FieldRows<MODE, 1>* c) {
 #pragma unroll
     for (int k = 0; k < C::K5; ++k) {
@@ -194,10 +206,10 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
       if constexpr (MODE == kFlowCoarse) centre(c[k], tb, k);
       const int gy = y0 + j;
       const bool out = j >= 0 && j < TH && (INTERIOR || (x0 + oc < W && gy < H));
-      const float* s = hs + r * HP + oc;
+      const float* s = win + r * VP + oc;
       const float2 f5 = c[k].at(0, gy, gy);
       float un, vn;
-      solve_update(s[0], s[NR * HP], s[2 * NR * HP], s[3 * NR * HP], s[4 * NR * HP], f5.x, f5.y,
+      solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
                    un, vn);
       const unsigned o = rowofs(gy, W, x0 + oc);
       if (pixel_mask) {   // masked-out pixels: zero flow
@@ -398,22 +410,51 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
 #pragma unroll
       for (int k = 0; k < C::K5; ++k) centre(c5[k], tb, k);
     }
-    static_assert(!GAUSS || BB == 1, "Gaussian-weighted window: one band per pass");
-    if (GAUSS && p4) {
+    if (GAUSS && BB == 2 && p4) {
+      // A tile of one pass: its output rows 2R .. 4R have their whole windows in the pass, M rows
+      // per thread, each the taps in order from the window's top row.
+      constexpr int M = (N + P4S - 1) / P4S;
+      const int top = min(vq * M, N - 1);
+      const float* col = hs + vk * NR * HP + vc;
+      float x[M + 2 * R];
+#pragma unroll
+      for (int i = 0; i < M + 2 * R; ++i) x[i] = col[min(top + i, NR - 1) * HP];
+      float* dst = pr + (vk * NR + 2 * R + top) * PP + vc;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q <= 2 * R; ++q) s = fmaf(a.taps[q], x[m + q], s);
+        if (top + m < N) dst[m * PP] = s;
+      }
+    } else if (GAUSS && p4) {
       // Output row r of the band: previous-band rows r+1..N-1 then current rows 0..r, i.e.
-      // window offsets 0..N-1 from its top row, weighted by the taps in that order.
-      float* col = hs + vk * N * HP + vc;
+      // window offsets 0..N-1 from its top row, weighted by the taps in that order.  A tile's
+      // first band has one output row, its last.
+      const float* col = hs + vk * N * HP + vc;
+      float* dst = pr + vk * N * PP + vc;
       float cur[N];
 #pragma unroll
       for (int r = 0; r < N; ++r) cur[r] = col[r * HP];
+      auto rows = [&](auto first, auto last) {
 #pragma unroll
-      for (int r = 0; r < N; ++r) {
-        float s = 0.f;
+        for (int r = decltype(first)::value; r <= decltype(last)::value; ++r) {
+          float s = 0.f;
 #pragma unroll
-        for (int m = r + 1; m < N; ++m) s = fmaf(a.taps[m - r - 1], prev[m], s);
+          for (int m = r + 1; m < N; ++m) s = fmaf(a.taps[m - r - 1], prev[m], s);
 #pragma unroll
-        for (int m = 0; m <= r; ++m) s = fmaf(a.taps[N - 1 - r + m], cur[m], s);
-        col[r * HP] = s;
+          for (int m = 0; m <= r; ++m) s = fmaf(a.taps[N - 1 - r + m], cur[m], s);
+          dst[r * PP] = s;
+        }
+      };
+      using std::integral_constant;
+      constexpr int kCut = P4S == 2 ? R : -1;   // last row of the first part
+      if (b == 0) {
+        if (vq == P4S - 1) rows(integral_constant<int, N - 1>{}, integral_constant<int, N - 1>{});
+      } else if (P4S == 2 && vq == 0) {
+        rows(integral_constant<int, 0>{}, integral_constant<int, kCut>{});
+      } else {
+        rows(integral_constant<int, kCut + 1>{}, integral_constant<int, N - 1>{});
       }
 #pragma unroll
       for (int r = 0; r < N; ++r) prev[r] = cur[r];
@@ -576,16 +617,18 @@ hipError_t go_plain_g(const IterArgs& a, int nb, int variant, hipStream_t s) {
     case kTileWide:
     case kTileWideLean: return go_plain_v<T, R, MODE, true, GAUSS>(a, nb, s);
   }
-  if constexpr (!GAUSS) {   // narrow strips: box window only
-    switch (variant) {
+  if constexpr (!GAUSS) {
+    switch (variant) {   // narrow strips, one band per pass: box window only
       case kTileWide32: return go_plain_v<T, R, MODE, true, false, 32>(a, nb, s);
       case kTileWide16: return go_plain_v<T, R, MODE, true, false, 16>(a, nb, s);
     }
-    if constexpr (R <= kMaxPairRadius) {   // two bands per pass
+  }
+  if constexpr (R <= kMaxPairRadius) {   // two bands per pass (Gaussian: tiles of one pass)
+    if (!GAUSS || nb == 1) {
       switch (variant) {
         case kTileWide32x2:
-        case kTileLean32x2: return go_plain_v<T, R, MODE, true, false, 32, 2>(a, nb, s);
-        case kTileWide16x2: return go_plain_v<T, R, MODE, true, false, 16, 2>(a, nb, s);
+        case kTileLean32x2: return go_plain_v<T, R, MODE, true, GAUSS, 32, 2>(a, nb, s);
+        case kTileWide16x2: return go_plain_v<T, R, MODE, true, GAUSS, 16, 2>(a, nb, s);
       }
     }
   }

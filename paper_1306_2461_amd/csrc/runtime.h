@@ -25,6 +25,7 @@ struct Geometry {
   size_t off_flow[4];               // ping-pong u0, u1, v0, v1 (level-0 size each)
   int nb[OF_MAX_LEVELS];            // iteration tile height per level, in bands of 2R+1 rows
   int variant[OF_MAX_LEVELS];       // tile variant of the iteration kernel (TileVariant)
+  int one_band[OF_MAX_LEVELS];      // Gaussian window, tiles of one output band: variant that runs them
   const uint8_t* mask[OF_MAX_LEVELS];   // per-level masks (of_plan_set_mask) or nullptr
   const uint8_t* tflags[OF_MAX_LEVELS]; // per-level iteration-tile flags (with a mask)
   const float* bthr;                // eq. 3 count of the final field (of_plan_set_bubble)
@@ -147,7 +148,7 @@ struct PlaneSize {
 };
 // Estimated time of one iteration launch over n planes with tile variant `variant` and tiles of nb
 // bands, in units of one band of a lone wide tile (see the definition).
-double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb);
+double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gauss);
 // The tile height of least estimated cost among `cand`.
 int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, int ncand);
 bool check_params(int H, int W, int levels, int radius, int iters, unsigned flags);

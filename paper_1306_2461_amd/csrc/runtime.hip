@@ -47,13 +47,23 @@ bool check_params(int H, int W, int levels, int radius, int iters, unsigned flag
 // model): 2048^2 at 8 bands 32.9 us / 16.8, 4 bands 36.3 / 18.8, 16 bands 42.1 / 19.3; 1024^2 at 2
 // bands 14.4 / 7.2, 3 bands 16.6 / 8.8, 4 bands 15.0 / 7.3; 16 x 1024^2 at 31 bands 123, 16 bands 123,
 // 8 bands 128, 4 bands 149, 2 bands 168 us.
-double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb) {
+// The Gaussian-weighted window's bands take longer (2 (2r+1) multiply-adds per product and sum),
+// those of a two-band pass less so, as its vertical sums spread over all threads.  Fitted at r = 4
+// and 8 on levels of 64^2 .. 1024^2, e.g. r = 8 (measured / model): 128^2 at one band in 64-column
+// strips 9.5 us / 2.9, two-band passes on 32 columns 6.3 / 2.0, on 16 columns 5.7 / 1.8; 512^2 9.8 /
+// 2.9, 9.1 / 2.8, 11.4 / 4.4; 1024^2 23.7 / 7.8, 24.9 / 8.6, 34.8 / 14, at two bands in 64-column
+// strips 19.2 / 5.8.
+double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gauss) {
   constexpr int kCus = 256;
   const TileShape sh = tile_shape(variant, R);
   const int N = 2 * R + 1;
   // cost of the launch and a tile's ends, and of a band, by strip width and bands per pass
-  const double base = sh.bb == 2 || sh.tw == 32 ? 1.5 : (sh.tw == 16 ? 1.0 : 2.0);
-  const double band = sh.bb == 2 ? (sh.tw == 16 ? 0.58 : 0.75) : (sh.tw == 16 ? 0.85 : (sh.tw == 32 ? 0.9 : 1.0));
+  double base = sh.bb == 2 || sh.tw == 32 ? 1.5 : (sh.tw == 16 ? 1.0 : 2.0);
+  double band = sh.bb == 2 ? (sh.tw == 16 ? 0.58 : 0.75) : (sh.tw == 16 ? 0.85 : (sh.tw == 32 ? 0.9 : 1.0));
+  if (gauss) {
+    base = R > 2 ? 5.0 / R : 2.0;
+    band = sh.bb == 2 ? std::min(0.8, sh.tw == 16 ? 0.98 - 0.0575 * R : 1.1 - 0.06 * R) : 1.0;
+  }
   long long tiles = 0;
   double work = 0, tall = 0;
   for (int i = 0; i < n; ++i) {
@@ -79,7 +89,7 @@ int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, i
   int best = cand[0];
   double cost = 1e300;
   for (int i = 0; i < ncand; ++i) {
-    const double c = iter_cost(s, n, R, variant, cand[i]);
+    const double c = iter_cost(s, n, R, variant, cand[i], false);
     if (c < cost) {
       cost = c;
       best = cand[i];
@@ -109,7 +119,7 @@ Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned
     double cost = 1e300;
     auto consider = [&](int variant, int step) {
       for (int nb = 1; nb <= 32; nb += step) {
-        const double c = iter_cost(&s, 1, radius, variant, nb);
+        const double c = iter_cost(&s, 1, radius, variant, nb, !box);
         if (c < cost) {
           cost = c;
           g.variant[l] = variant;
@@ -123,6 +133,23 @@ Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned
     if (box && radius <= kMaxPairRadius) {
       consider(kTileWide32x2, 2);
       consider(kTileWide16x2, 2);
+    }
+    // Gaussian window: tiles of one output band in 64-column strips run as two-band passes on 32
+    // or 16 columns where that costs less (the sums are the same, as always).
+    g.one_band[l] = kTileWide;
+    if (!box && radius <= kMaxPairRadius) {
+      double least = iter_cost(&s, 1, radius, kTileWide, 1, true);
+      for (int v : {kTileWide32x2, kTileWide16x2}) {
+        const double c = iter_cost(&s, 1, radius, v, 1, true);
+        if (c < least) {
+          least = c;
+          g.one_band[l] = v;
+        }
+      }
+      if (least < cost) {
+        g.variant[l] = kTileWide;
+        g.nb[l] = 1;
+      }
     }
   }
   g.ein = (flags & OF_FLAG_INPUT_F32) ? Elem::F32 : Elem::U8;
@@ -229,7 +256,7 @@ KernelTimer::~KernelTimer() {
   for (hipEvent_t e : pool) hipEventDestroy(e);
 }
 
-// Window taps and launch variant of one iteration: the Gaussian-weighted window
+// Window taps and launch variant of one iteration (its mask set): the Gaussian-weighted window
 // (OF_FLAG_GAUSSIAN_WINDOW) fills the taps g(d) = exp(-d^2 / (2 sigma^2)), sigma = r/2,
 // d = -r..r, and marks the variant.
 void gaussian_taps(float* taps, int R) {
@@ -278,7 +305,9 @@ void band_cut(const uint8_t* m, int W, int c0, int c1, int y0, int e, int N, int
 int window_variant(const Geometry& g, int l, IterArgs& a) {
   if (!(g.flags & OF_FLAG_GAUSSIAN_WINDOW)) return g.variant[l];
   gaussian_taps(a.taps, g.R);
-  return g.variant[l] | kTileGauss;
+  // (a mask's flags are those of 64-column tiles)
+  const int v = g.variant[l] != kTileNarrow && g.nb[l] == 1 && !a.mask ? g.one_band[l] : g.variant[l];
+  return v | kTileGauss;
 }
 
 // Enqueue the whole method for one pair: pyramid then levels x iterations.

@@ -106,3 +106,33 @@ def test_batch_default_heights(gpu_lib, sizes):
         assert torch.equal(u, us[i]) and torch.equal(v, vs[i]), i
         plan.close()
     b.close()
+
+
+@pytest.mark.parametrize("r", range(13))
+@pytest.mark.parametrize("shape", [(1, 1), (37, 18), (97, 129), (300, 390)])
+def test_gaussian_one_band_tiles(gpu_lib, r, shape):
+    """The Gaussian window's default tiles (up to r = 8 two-band passes on 16 or 32 columns on small
+    levels), tiles of one band and taller ones give the bits of the narrow variant, also under a mask
+    of ones (whose tiles keep 64 columns)."""
+    import torch
+    ofmi = gpu_lib
+    announce(f"gaussian one-band tiles r={r} {shape}")
+    I1, I2 = (to_dev(np.ascontiguousarray(np.pad(f, ((0, 140), (0, 200)), mode="reflect")[:shape[0], :shape[1]]))
+              for f in _frames(220, 220))
+    plan = ofmi.Plan(*shape, 1, r, 3, gaussian_window=True, device=dev())
+
+    def flow(bands=None, variant=None):
+        if bands:
+            plan.set_config({"bands": [bands], "variant": [variant]})
+        u, v = plan.compute(I1, I2)
+        torch.cuda.synchronize()
+        return torch.stack([u, v]).cpu().numpy().view(np.int32)
+
+    default = flow()
+    ref = flow(2, 0)
+    assert np.array_equal(default, ref)
+    for bands, variant in [(1, 1), (1, 2), (3, 1), (1, 0)]:
+        assert np.array_equal(flow(bands, variant), ref), (bands, variant)
+    plan.set_mask(torch.ones(shape, dtype=torch.uint8, device=dev()))
+    assert np.array_equal(flow(1, 1), ref)
+    plan.close()
