@@ -20,9 +20,12 @@ struct ReduceJob {
 };
 
 // Output tile of the pyramid reduction kernels (columns x rows of the coarser level).
+// 8-bit frames: a wave takes 128 columns, four waves the rows.
 constexpr int kReduceTileW = 64, kReduceTileH = 16;
-inline int reduce_blocks(int Ho, int Wo) {
-  return ((Wo + kReduceTileW - 1) / kReduceTileW) * ((Ho + kReduceTileH - 1) / kReduceTileH);
+constexpr int kU8TileW = 128, kU8TileH = 32;
+inline int reduce_blocks(Elem tin, int Ho, int Wo) {
+  const int tw = tin == Elem::U8 ? kU8TileW : kReduceTileW, th = tin == Elem::U8 ? kU8TileH : kReduceTileH;
+  return ((Wo + tw - 1) / tw) * ((Ho + th - 1) / th);
 }
 
 // Batched pyramid step over (job, output tile) work items.

@@ -70,6 +70,104 @@ __device__ __forceinline__ void reduce_tile(const Tin* __restrict__ in, int H, i
   }
 }
 
+// 8-bit frames: no LDS and no barriers, a lane holds the 5-tap rows of two output columns in
+// registers.  Their seven input pixels 2j-2 .. 2j+4 come as one 8-byte load per row from the window
+// of the row that holds them (start clamped into the row), and two byte permutations, formed once per
+// thread, put clamped pixel k at byte k.  A wave covers kU8TileW output columns and kU8WaveH rows:
+// 2 kU8WaveH + 3 loads in flight at once, about 25 vector instructions per input row and wave.
+// Bound by HBM; the staged form above spent its time on LDS reads at stride 2, barriers and
+// one-byte loads: 32 frames of 1024^2 to float32 27.4 us (2.4 TB/s), here 19.8 us (3.4 TB/s); a pair of
+// 2048^2 26.3 -> 9.1 us and of 1024^2 10.0 -> 6.6 us, which took one thread per output before.
+// The same FMA chains as reduce_tile: the same bits.
+constexpr int kU8WaveH = kU8TileH / 4;
+
+// Two successive outputs as one store.
+__device__ __forceinline__ void st2(float* p, unsigned i, float x, float y) {
+  typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+  *((global_t<f2>*)((global_t<char>*)p + i * 4u)) = f2{x, y};
+}
+__device__ __forceinline__ void st2(__half* p, unsigned i, float x, float y) {
+  typedef unsigned u1 __attribute__((aligned(2)));
+  const unsigned lo = __half_as_ushort(__float2half_rn(x)), hi = __half_as_ushort(__float2half_rn(y));
+  *((global_t<u1>*)((global_t<char>*)p + i * 2u)) = lo | hi << 16;
+}
+
+template <typename Tout>
+__device__ __forceinline__ void reduce_u8_tile(const uint8_t* __restrict__ in, int H, int W,
+                                               Tout* __restrict__ out, int Ho, int Wo, int bx, int by) {
+  const int i0 = by * kU8TileH + (int)(threadIdx.x >> 6) * kU8WaveH;   // the wave's first output row
+  const int j = bx * kU8TileW + 2 * (int)(threadIdx.x & 63);           // the lane's first output column
+  if (i0 >= Ho) return;
+  constexpr int NR = 2 * kU8WaveH + 3;
+  unsigned lo[NR], hi[NR];   // pixels 2j-2 .. 2j+1 and 2j+2 .. 2j+4 of the rows from 2 i0 - 2
+  if (W >= 8) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2), aligned(1)));
+    const int base = min(max(2 * j - 2, 0), W - 8);
+    unsigned slo = 0, shi = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      slo |= (unsigned)(min(max(2 * j - 2 + k, 0), W - 1) - base) << (8 * k);
+      if (k < 3) shi |= (unsigned)(min(max(2 * j + 2 + k, 0), W - 1) - base) << (8 * k);
+    }
+    u2 w[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const unsigned y = (unsigned)min(max(2 * i0 - 2 + k, 0), H - 1);
+      w[k] = *((const global_t<u2>*)((const global_t<uint8_t>*)in + (y * (unsigned)W + (unsigned)base)));
+    }
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      lo[k] = __builtin_amdgcn_perm(w[k].y, w[k].x, slo);
+      hi[k] = __builtin_amdgcn_perm(w[k].y, w[k].x, shi);
+    }
+  } else {   // rows shorter than the window: pixel by pixel
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const unsigned row = (unsigned)min(max(2 * i0 - 2 + k, 0), H - 1) * (unsigned)W;
+      lo[k] = hi[k] = 0;
+      for (int q = 0; q < 4; ++q) {
+        lo[k] |= (unsigned)at(in, row + (unsigned)min(max(2 * j - 2 + q, 0), W - 1)) << (8 * q);
+        hi[k] |= (unsigned)at(in, row + (unsigned)min(max(2 * j + 2 + q, 0), W - 1)) << (8 * q);
+      }
+    }
+  }
+  float h0[NR], h1[NR];   // row results at columns j, j + 1
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    auto px = [&](int q) { return (float)((q < 4 ? lo[k] >> (8 * q) : hi[k] >> (8 * (q - 4))) & 255u); };
+    auto row = [&](int q) {
+      float acc = kB0 * px(q);
+      acc = fmaf(kB1, px(q + 1), acc);
+      acc = fmaf(kB2, px(q + 2), acc);
+      acc = fmaf(kB1, px(q + 3), acc);
+      return fmaf(kB0, px(q + 4), acc);
+    };
+    h0[k] = row(0);
+    h1[k] = row(2);
+  }
+#pragma unroll
+  for (int p = 0; p < kU8WaveH; ++p) {
+    auto col = [&](const float* h) {
+      float acc = kB0 * h[0];
+      acc = fmaf(kB1, h[1], acc);
+      acc = fmaf(kB2, h[2], acc);
+      acc = fmaf(kB1, h[3], acc);
+      return fmaf(kB0, h[4], acc);
+    };
+    const float a = col(h0 + 2 * p), b = col(h1 + 2 * p);
+    const unsigned o = (unsigned)(i0 + p) * (unsigned)Wo + (unsigned)j;
+    if (i0 + p < Ho && j + 1 < Wo) st2(out, o, a, b);
+    else if (i0 + p < Ho && j < Wo) st(out, o, a);
+  }
+}
+
+template <typename Tout>
+__global__ __launch_bounds__(256) void reduce_u8_kernel(const uint8_t* __restrict__ in1, const uint8_t* __restrict__ in2,
+                                                        int H, int W, Tout* __restrict__ out1,
+                                                        Tout* __restrict__ out2, int Ho, int Wo) {
+  reduce_u8_tile<Tout>(blockIdx.z ? in2 : in1, H, W, blockIdx.z ? out2 : out1, Ho, Wo, blockIdx.x, blockIdx.y);
+}
+
 template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void reduce_kernel(const Tin* __restrict__ in1,
                                                       const Tin* __restrict__ in2, int H, int W,
@@ -122,15 +220,24 @@ template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void reduce_batch_kernel(const ReduceJob* __restrict__ jobs,
                                                             const int2* __restrict__ items,
                                                             int nitems) {
-  __shared__ float win[IH * IWP];
-  __shared__ float hrow[IH * TW];
-  for (int t = blockIdx.x; t < nitems; t += gridDim.x) {
-    const int2 it = items[t];
-    const ReduceJob jb = jobs[it.x];
-    const int bxn = (jb.Wo + TW - 1) / TW;
-    reduce_tile<Tin, Tout>((const Tin*)jb.in, jb.H, jb.W, (Tout*)jb.out, jb.Ho, jb.Wo,
-                           it.y % bxn, it.y / bxn, win, hrow);
-    __syncthreads();
+  if constexpr (sizeof(Tin) == 1) {
+    for (int t = blockIdx.x; t < nitems; t += gridDim.x) {
+      const int2 it = items[t];
+      const ReduceJob jb = jobs[it.x];
+      const int bxn = (jb.Wo + kU8TileW - 1) / kU8TileW;
+      reduce_u8_tile<Tout>((const uint8_t*)jb.in, jb.H, jb.W, (Tout*)jb.out, jb.Ho, jb.Wo, it.y % bxn, it.y / bxn);
+    }
+  } else {
+    __shared__ float win[IH * IWP];
+    __shared__ float hrow[IH * TW];
+    for (int t = blockIdx.x; t < nitems; t += gridDim.x) {
+      const int2 it = items[t];
+      const ReduceJob jb = jobs[it.x];
+      const int bxn = (jb.Wo + TW - 1) / TW;
+      reduce_tile<Tin, Tout>((const Tin*)jb.in, jb.H, jb.W, (Tout*)jb.out, jb.Ho, jb.Wo,
+                             it.y % bxn, it.y / bxn, win, hrow);
+      __syncthreads();
+    }
   }
 }
 
@@ -141,12 +248,16 @@ hipError_t go_batch(const ReduceJob* jobs, const int2* items, int nitems, int gr
   return hipGetLastError();
 }
 
-// Planes of up to 2^20 output pixels take the direct form (a single pair's pyramid step is
-// latency bound), larger ones the staged form.
+// 8-bit frames take the register form; other planes of up to 2^20 output pixels the direct form (a
+// single pair's pyramid step is latency bound), larger ones the staged form.
 template <typename Tin, typename Tout>
 hipError_t go(const void* in1, const void* in2, int H, int W, void* out1, void* out2, int Ho,
               int Wo, hipStream_t s) {
-  if ((long long)Ho * Wo <= (1ll << 20)) {
+  if constexpr (sizeof(Tin) == 1) {
+    dim3 grid((Wo + kU8TileW - 1) / kU8TileW, (Ho + kU8TileH - 1) / kU8TileH, in2 ? 2 : 1);
+    hipLaunchKernelGGL((reduce_u8_kernel<Tout>), grid, dim3(256), 0, s, (const uint8_t*)in1, (const uint8_t*)in2, H,
+                       W, (Tout*)out1, (Tout*)out2, Ho, Wo);
+  } else if ((long long)Ho * Wo <= (1ll << 20)) {
     dim3 grid((Wo + 63) / 64, (Ho + 3) / 4, in2 ? 2 : 1);
     hipLaunchKernelGGL((reduce_direct_kernel<Tin, Tout>), grid, dim3(256), 0, s, (const Tin*)in1,
                        (const Tin*)in2, H, W, (Tout*)out1, (Tout*)out2, Ho, Wo);

@@ -342,8 +342,12 @@ hipError_t enqueue_pair(const Geometry& g, char* ws, const void* I1, const void*
     P1[l] = ws + g.off_p1[l];
     P2[l] = ws + g.off_p2[l];
   }
-  // Pyramid: runs of 2 or 3 levels whose first output plane has at most 2^20 pixels take one
-  // fused chain launch each, other levels one reduction each (identical bits either way).
+  // Pyramid: runs of 2 or 3 levels whose first output plane is small take one fused chain launch
+  // each, other levels one reduction each (identical bits either way).  A chain recomputes its
+  // tiles' margins at every level but saves launches: up to 2^20 pixels, from 8-bit frames, whose
+  // single reduction is fast, up to 2^18 (three levels) or 7 * 2^17 (two).  Pyramid of a pair,
+  // chain / first level by itself: 1024^2 L4 9.0 us / 11.3, 1300^2 13.5 / 12.9, 2048^2 20.6 / 14.7;
+  // 1024^2 L3 7.6 / 10.8, 1448^2 12.4 / 14.7, 1800^2 15.5 / 16.4, 2048^2 16.7 / 15.8.
   hipEvent_t span = nullptr;
   double span_units = 0, span_bytes = 0;
   long long span_launches = 0;
@@ -353,7 +357,8 @@ hipError_t enqueue_pair(const Geometry& g, char* ws, const void* I1, const void*
   }
   for (int l = 1; l < g.L;) {
     const int rest = g.L - l;
-    const int D = (rest >= 2 && (long long)g.H[l] * g.W[l] <= (1ll << 20)) ? (rest >= 3 ? 3 : 2) : 1;
+    const long long most = g.elem(l - 1) != Elem::U8 ? 1ll << 20 : (rest >= 3 ? 1ll << 18 : 7ll << 17);
+    const int D = (rest >= 2 && (long long)g.H[l] * g.W[l] <= most) ? (rest >= 3 ? 3 : 2) : 1;
     hipEvent_t ev;
     hipError_t e = t && t->per_launch() ? t->begin(s, &ev) : hipSuccess;
     if (e == hipSuccess) {

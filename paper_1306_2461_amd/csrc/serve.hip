@@ -182,7 +182,7 @@ size_t push_bound(const std::vector<of_session*>& ss, int L, int R, int K) {
   size_t b = 0;
   for (int l = 1; l < L; ++l) {
     size_t items = 0;
-    for (const of_session* x : ss) items += reduce_blocks(x->g.H[l], x->g.W[l]);
+    for (const of_session* x : ss) items += reduce_blocks(x->g.elem(l - 1), x->g.H[l], x->g.W[l]);
     b += align256(n * sizeof(ReduceJob)) + align256(items * sizeof(int2));
   }
   b += (size_t)L * (K > 0 ? K : 0) * align256(n * sizeof(IterArgs));
@@ -405,7 +405,7 @@ of_status of_server_push(of_server* s, of_session* const* ss, int n, const void*
       const int job = (int)p.jobs[l - 1].size();
       p.jobs[l - 1].push_back({x->mem + x->slot_off[x->cur][l - 1], x->mem + x->slot_off[x->cur][l],
                                x->g.H[l - 1], x->g.W[l - 1], x->g.H[l], x->g.W[l]});
-      const int blocks = reduce_blocks(x->g.H[l], x->g.W[l]);
+      const int blocks = reduce_blocks(x->g.elem(l - 1), x->g.H[l], x->g.W[l]);
       for (int k = 0; k < blocks; ++k) p.items[l - 1].push_back(make_int2(job, k));
     }
   std::vector<int> flowing;
