@@ -28,9 +28,12 @@ inline size_t normalize_lds_bytes(int r) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void normalize_kernel(const T* __restrict__ in, float* __restrict__ out,
+__global__ __launch_bounds__(256) void normalize_kernel(const T* __restrict__ in1, const T* __restrict__ in2,
+                                                        float* __restrict__ out1, float* __restrict__ out2,
                                                         int H, int W, int r, float eps) {
   extern __shared__ double rs[];     // [rows * NTW] sums, the same of squares, then the window
+  const T* in = blockIdx.z ? in2 : in1;
+  float* out = blockIdx.z ? out2 : out1;
   const int x0 = blockIdx.x * NTW, y0 = blockIdx.y * NTH;
   const int rows = NTH + 2 * r, cols = NTW + 2 * r;
   double* s1 = rs;
@@ -101,15 +104,33 @@ __global__ __launch_bounds__(256) void normalize_kernel(const T* __restrict__ in
 // same bits after the FP64 division and square root below.
 constexpr int kSeg = 8;              // outputs per thread of a sliding row or column sum
 
+// a / n for integers 0 <= a < 2^31 and 1 <= n <= 33 * 33, rn = 1 / n rounded: the product's
+// remainder a - n q is exact and q plus its share differs from a / n by less than 2^-52 ulp, while
+// a / n, no tie (at most 31 significant bits), is at least 1 / (2 n) ulp off every rounding
+// boundary: the bits of the division.
+__device__ __forceinline__ double quotient(double a, double n, double rn) {
+  const double q = a * rn;
+  return fma(fma(-n, q, a), rn, q);
+}
+
 inline size_t normalize_u8_lds_bytes(int r) {
   const size_t rows = NTH + 2 * (size_t)r, cols = NTW + 2 * (size_t)r;
   return sizeof(int) * (2 * rows * NTW + rows * cols);
 }
 
-__global__ __launch_bounds__(256) void normalize_u8_kernel(const uint8_t* __restrict__ in,
-                                                           float* __restrict__ out, int H, int W,
-                                                           int r, float eps) {
+// RC: the radius at compile time (that of a plan's frames: the window's loads and sums unroll and
+// their index divisions become multiplications), -1: at run time.  Both frames of a pair take one
+// launch.  A 384 x 1792 pair, r = 5: two launches of 9.0 us before, one of 11.2 us here; bound by the
+// integer sums' LDS passes and the FP64 root and division of every pixel.
+template <int RC>
+__global__ __launch_bounds__(256) void normalize_u8_kernel(const uint8_t* __restrict__ in1,
+                                                           const uint8_t* __restrict__ in2,
+                                                           float* __restrict__ out1, float* __restrict__ out2,
+                                                           int H, int W, int radius, float eps) {
   extern __shared__ int ri[];        // [rows * NTW] sums of I, the same of I^2, then the window
+  const uint8_t* in = blockIdx.z ? in2 : in1;
+  float* out = blockIdx.z ? out2 : out1;
+  const int r = RC >= 0 ? RC : radius;
   const int x0 = blockIdx.x * NTW, y0 = blockIdx.y * NTH;
   const int rows = NTH + 2 * r, cols = NTW + 2 * r;
   int* s1 = ri;
@@ -163,7 +184,8 @@ __global__ __launch_bounds__(256) void normalize_u8_kernel(const uint8_t* __rest
   constexpr int RG = NTH / 4;
   const int lx = threadIdx.x % NTW, ly0 = (threadIdx.x / NTW) * RG;
   const int gx = x0 + lx;
-  int a = 0, b = 0;
+  int a = 0, b = 0, ny0 = 0;
+  double n = 1.0, rn = 1.0;
   for (int dy = 0; dy <= 2 * r; ++dy) {
     a += s1[(ly0 + dy) * NTW + lx];
     b += s2[(ly0 + dy) * NTW + lx];
@@ -177,8 +199,12 @@ __global__ __launch_bounds__(256) void normalize_u8_kernel(const uint8_t* __rest
     if (gy >= H || gx >= W) continue;
     const int nx = min(gx + r, W - 1) - max(gx - r, 0) + 1;
     const int ny = min(gy + r, H - 1) - max(gy - r, 0) + 1;
-    const double n = (double)nx * ny;
-    const double m = (double)a / n, m2 = (double)b / n;
+    if (ny != ny0) {
+      ny0 = ny;
+      n = (double)nx * ny;
+      rn = 1.0 / n;
+    }
+    const double m = quotient((double)a, n, rn), m2 = quotient((double)b, n, rn);
     const double sd = sqrt(fmax(m2 - m * m, 0.0));
     const double c = (double)win[(ly0 + j + r) * cols + lx + r];
     at(out, (unsigned)gy * (unsigned)W + (unsigned)gx) = (float)((c - m) / (sd + (double)eps));
@@ -320,22 +346,23 @@ hipError_t launch_count_at_most(const float* x, long long n, const float* thr,
   return hipGetLastError();
 }
 
-hipError_t launch_normalize(Elem t, const void* in, float* out, int H, int W, int r, float eps,
-                            hipStream_t s) {
+hipError_t launch_normalize(Elem t, const void* in1, const void* in2, float* out1, float* out2, int H, int W,
+                            int r, float eps, hipStream_t s) {
   if (r < 0 || r > OF_MAX_NORMALIZE_RADIUS) return hipErrorInvalidValue;
-  dim3 grid((W + NTW - 1) / NTW, (H + NTH - 1) / NTH);
+  dim3 grid((W + NTW - 1) / NTW, (H + NTH - 1) / NTH, in2 ? 2 : 1);
   const size_t lds = normalize_lds_bytes(r);
   // Up to 67.5 KB at the largest radius: opt in to more than 64 KB of dynamic LDS, once.
   static const hipError_t opt32 = hipFuncSetAttribute(
       reinterpret_cast<const void*>(&normalize_kernel<float>),
       hipFuncAttributeMaxDynamicSharedMemorySize, (int)normalize_lds_bytes(OF_MAX_NORMALIZE_RADIUS));
   if (t == Elem::U8) {
-    hipLaunchKernelGGL(normalize_u8_kernel, grid, dim3(256), normalize_u8_lds_bytes(r), s,
-                       (const uint8_t*)in, out, H, W, r, eps);
+    hipLaunchKernelGGL(r == OF_NORMALIZE_RADIUS ? normalize_u8_kernel<OF_NORMALIZE_RADIUS> : normalize_u8_kernel<-1>,
+                       grid, dim3(256), normalize_u8_lds_bytes(r), s, (const uint8_t*)in1, (const uint8_t*)in2,
+                       out1, out2, H, W, r, eps);
   } else if (t == Elem::F32) {
     if (opt32 != hipSuccess) return opt32;
-    hipLaunchKernelGGL(normalize_kernel<float>, grid, dim3(256), lds, s, (const float*)in, out, H,
-                       W, r, eps);
+    hipLaunchKernelGGL(normalize_kernel<float>, grid, dim3(256), lds, s, (const float*)in1, (const float*)in2, out1,
+                       out2, H, W, r, eps);
   } else {
     return hipErrorInvalidValue;
   }
@@ -356,7 +383,7 @@ of_status of_normalize(const void* in, float* out, int H, int W, int radius, flo
   if (!(eps >= 0.f)) return set_error("eps must be >= 0"), OF_EINVAL;
   if (flags & ~OF_FLAG_INPUT_F32) return set_error("unknown flags"), OF_EINVAL;
   if ((void*)out == in) return set_error("in and out must differ"), OF_EINVAL;
-  hipError_t e = launch_normalize((flags & OF_FLAG_INPUT_F32) ? Elem::F32 : Elem::U8, in, out, H,
+  hipError_t e = launch_normalize((flags & OF_FLAG_INPUT_F32) ? Elem::F32 : Elem::U8, in, nullptr, out, nullptr, H,
                                   W, radius, eps, (hipStream_t)stream);
   if (e != hipSuccess) return set_error(std::string("normalize: ") + hipGetErrorString(e)), OF_EHIP;
   return OF_OK;

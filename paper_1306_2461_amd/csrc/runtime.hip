@@ -330,10 +330,8 @@ hipError_t enqueue_pair(const Geometry& g, char* ws, const void* I1, const void*
   if (g.flags & OF_FLAG_NORMALIZE) {
     float* n1 = (float*)(ws + g.off_norm[0]);
     float* n2 = (float*)(ws + g.off_norm[1]);
-    hipError_t e = launch_normalize(g.ein, I1, n1, g.H[0], g.W[0], OF_NORMALIZE_RADIUS,
+    hipError_t e = launch_normalize(g.ein, I1, I2, n1, n2, g.H[0], g.W[0], OF_NORMALIZE_RADIUS,
                                     OF_NORMALIZE_EPS, s);
-    if (e == hipSuccess)
-      e = launch_normalize(g.ein, I2, n2, g.H[0], g.W[0], OF_NORMALIZE_RADIUS, OF_NORMALIZE_EPS, s);
     if (e != hipSuccess) return e;
     P1[0] = n1;
     P2[0] = n2;
