@@ -140,8 +140,22 @@ hipError_t launch_zero_tiles(const IterArgs* args, const int4* tiles, int ntiles
                              hipStream_t s);
 // Loads the zero-tiles kernel's code on the current device (no launch).
 hipError_t prime_zero_tiles();
-// Copy of `bytes` bytes by a kernel on stream s (device memory, or pinned host memory through
-// its device mapping).
+// Copies of device memory, or of pinned host memory through its device mapping, by one kernel on
+// stream s.
+struct CopyJobs {
+  static constexpr int kMost = 16;
+  void* dst[kMost];
+  const void* src[kMost];
+  size_t bytes[kMost];
+  int n = 0;
+  bool full() const { return n == kMost; }
+  void add(void* d, const void* s, size_t b) {
+    dst[n] = d;
+    src[n] = s;
+    bytes[n++] = b;
+  }
+};
+hipError_t launch_copies(const CopyJobs& jobs, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 
 // *c = 0 (a one-thread kernel, safe under stream capture).

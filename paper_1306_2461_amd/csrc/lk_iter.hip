@@ -97,8 +97,13 @@ __global__ __launch_bounds__(256) void zero_tiles_kernel(const IterArgs* __restr
   }
 }
 
-// dst[0..bytes) = src[0..bytes): 16-byte words when both are 16-byte aligned, then the tail.
-__global__ void copy_kernel(char* __restrict__ dst, const char* __restrict__ src, size_t bytes) {
+// dst[0..bytes) = src[0..bytes) of job blockIdx.y: 16-byte words when both are 16-byte aligned, then
+// the tail.  One launch for a push's frames and arguments: a launch each took 4.5 to 6.3 us on the
+// stream, 44 us of a push of eight frames (12.9 MB), all together 7.8 us.
+__global__ __launch_bounds__(256) void copy_kernel(CopyJobs jobs) {
+  char* __restrict__ dst = (char*)jobs.dst[blockIdx.y];
+  const char* __restrict__ src = (const char*)jobs.src[blockIdx.y];
+  const size_t bytes = jobs.bytes[blockIdx.y];
   const size_t tid = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   size_t done = 0;
@@ -127,12 +132,19 @@ hipError_t prime_zero_tiles() {
   return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&zero_tiles_kernel));
 }
 
-hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
-  if (bytes == 0) return hipSuccess;
-  const size_t words = (bytes + 15) / 16;
+hipError_t launch_copies(const CopyJobs& jobs, hipStream_t s) {
+  size_t words = 0;
+  for (int i = 0; i < jobs.n; ++i) words = std::max(words, (jobs.bytes[i] + 15) / 16);
+  if (words == 0) return hipSuccess;
   const unsigned grid = (unsigned)std::min<size_t>((words + 255) / 256, 1024);
-  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(256), 0, s, (char*)dst, (const char*)src, bytes);
+  hipLaunchKernelGGL(copy_kernel, dim3(grid, (unsigned)jobs.n), dim3(256), 0, s, jobs);
   return hipGetLastError();
+}
+
+hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  CopyJobs jobs;
+  jobs.add(dst, src, bytes);
+  return launch_copies(jobs, s);
 }
 
 namespace {

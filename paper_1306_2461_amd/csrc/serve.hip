@@ -512,12 +512,17 @@ of_status of_server_push(of_server* s, of_session* const* ss, int n, const void*
   // the calling thread for about 9 ms once in a few hundred pushes, which dominated the
   // latency tail of served streams.
   hipError_t e = hipSuccess;
+  CopyJobs copies;
+  copies.add(dblk, s->host_blk_dev + (size_t)slot * s->slot_bytes, p.bytes);
   for (int i = 0; i < n && e == hipSuccess; ++i) {
     of_session* x = ss[i];
-    e = launch_copy(x->mem + x->slot_off[x->cur][0], frames[i],
-                    (size_t)x->H * x->W * elem_bytes(x->g.e0), st);
+    copies.add(x->mem + x->slot_off[x->cur][0], frames[i], (size_t)x->H * x->W * elem_bytes(x->g.e0));
+    if (copies.full()) {
+      e = launch_copies(copies, st);
+      copies.n = 0;
+    }
   }
-  if (e == hipSuccess) e = launch_copy(dblk, s->host_blk_dev + (size_t)slot * s->slot_bytes, p.bytes, st);
+  if (e == hipSuccess) e = launch_copies(copies, st);
   if (e != hipSuccess) return hip_fail("push copies", e);
   // 3. new pyramids, then the iterations of the flowing sessions
   for (int l = 1; l < L && e == hipSuccess; ++l) {
