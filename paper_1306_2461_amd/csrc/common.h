@@ -220,13 +220,20 @@ template <int K>
 struct FieldRows<kFlowCoarse, K> {
   static constexpr int NP = (K + 1) / 2;
   float u00[NP], u01[NP], u10[NP], u11[NP], v00[NP], v01[NP], v10[NP], v11[NP], fa;
-  // Pair p, whose first row is y.
+  // Pair p, whose first row is y.  INTERIOR: the coarse row and column after the base exist.
+  template <bool INTERIOR>
   __device__ __forceinline__ void issue(int p, const Plane<float>& U, const Plane<float>& V, int Hc, int Wc, int x,
                                         int y) {
     const int x0 = x >> 1, y0 = y >> 1;
+    fa = (x & 1) ? 0.5f : 0.f;
+    if constexpr (INTERIOR) {
+      const unsigned o = rowofs(y0, Wc, x0);
+      u00[p] = U.ld(o, 0), u01[p] = U.ld(o + 1u, 0), u10[p] = U.ld(o, Wc), u11[p] = U.ld(o + 1u, Wc);
+      v00[p] = V.ld(o, 0), v01[p] = V.ld(o + 1u, 0), v10[p] = V.ld(o, Wc), v11[p] = V.ld(o + 1u, Wc);
+      return;
+    }
     const unsigned dx = x0 < Wc - 1 ? 1u : 0u;
     const unsigned dy = y0 < Hc - 1 ? (unsigned)Wc : 0u;
-    fa = (x & 1) ? 0.5f : 0.f;
     const unsigned i00 = rowofs(y0, Wc, x0);
     const unsigned i01 = i00 + dx, i10 = i00 + dy, i11 = i00 + dy + dx;
     u00[p] = U.ld(i00, 0), u01[p] = U.ld(i01, 0), u10[p] = U.ld(i10, 0), u11[p] = U.ld(i11, 0);

@@ -70,6 +70,11 @@ struct Cfg {
   static constexpr size_t HS_FLOATS = 5 * (size_t)NR * HP;
   static constexpr size_t FC_FLOATS = 2 * (size_t)G * WP;
   static constexpr size_t LDS_BYTES = (PR_FLOATS + W2_FLOATS + HS_FLOATS + FC_FLOATS) * sizeof(float);
+  // Launches that hand their field rows on to P5: u and v at the strip's columns and the RING sampled
+  // rows that P5 still needs, row t of the tile at t % RING (r <= 8: 77.6 KB in all at most, still two
+  // workgroups per CU).
+  static constexpr int RING = NR + R + 1;
+  static constexpr size_t HANDED_LDS_BYTES = LDS_BYTES + 2 * (size_t)RING * TW * sizeof(float);
 };
 
 // Wavefronts per SIMD the register allocation aims at: two workgroups of a wide variant share a

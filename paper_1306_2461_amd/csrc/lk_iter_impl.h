@@ -58,6 +58,17 @@ __device__ __forceinline__ void add_count(unsigned long long* dst, unsigned c) {
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(dst, (unsigned long long)c);
 }
 
+// Whether a launch hands its field rows on to P5 through LDS instead of reading the field planes
+// again: from a coarser level a pixel's field takes eight loads and two interpolations.  Batched
+// launches only (16 pairs of 1024^2, first iteration of level 0: 138.9 -> 124.1 us; a plan's tiles are
+// shorter: 2048^2 level 0 32.3 us either way), and not of 16-bit frames, whose samples leave no
+// registers for it (24 mixed pairs, level 1: 75.9 us, handed on 86.0 us with 36 bytes of scratch).
+// r = 0 outputs a row above a tile's first sampled rows.
+template <typename T, int R, int MODE, bool GAUSS, bool BUB>
+constexpr bool field_handed() {
+  return R > 0 && MODE == kFlowCoarse && !GAUSS && !BUB && sizeof(T) != 2;
+}
+
 // One tile: TW output columns from x0 = bx*TW and TH output rows from row y0, walked in
 // nbands bands (TH is a multiple of N; nbands = TH/N + 1).  `sm4` is the workgroup's LDS.
 // INTERIOR: the tile's whole warped-frame region (the tile grown by r + 1 px, all bands)
@@ -85,6 +96,8 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   float* hs = w2 + C::W2_FLOATS;                // [5][NR][HP] horizontal, then window sums
   float* fcu = hs + C::HS_FLOATS;               // [G][WP] field rows passed on to P2
   float* fcv = fcu + G * WP;
+  float* ru = fcv + G * WP;                     // [RING][TW] field rows passed on to P5
+  float* rv = ru + C::RING * TW;
 
   // Opaque per tile, so that a work-list kernel forms what depends on it per tile instead of
   // keeping it in registers across the tiles of both paths.
@@ -128,11 +141,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
       }
     } else if constexpr (MODE == kFlowCoarse) {
 #pragma unroll
-      for (int k = 0; k < K; k += 2) f.issue(k / 2, U, V, a.Hc, a.Wc, gx, min(row_at(ys + k, i), H - 1));
+      for (int k = 0; k < K; k += 2)
+        f.template issue<INTERIOR>(k / 2, U, V, a.Hc, a.Wc, gx, INTERIOR ? ys + k + i : row_at(ys + k, i));
     }
   };
   auto field_at = [&](const auto& f, int ys, int i, int k) {
-    return f.at(k, min(row_at(ys + k, i), H - 1), min(row_at(ys + k / 2 * 2, i), H - 1));
+    return f.at(k, row_at(ys + k, i), row_at(ys + k / 2 * 2, i));
   };
   // Frame 1 one row above this thread's k-th row of the pass whose LDS row 0 is image row yw.
   auto frame1 = [&](int yw, int k) {
@@ -179,12 +193,18 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     }
   };
 
+  // HANDED: the field rows go on to P5 in LDS.  ring_row is the slot of the pass's first sampled row;
+  // P2 writes them: every wave has then left P5 of the pass before.
+  constexpr bool HANDED = field_handed<T, R, MODE, GAUSS, BUB>();
+  constexpr int RING = C::RING;
+  int ring_row = 0;
+  auto wrap = [](int s) { return s >= RING ? s - RING : s; };
   // Field at this thread's output pixel of round k (clamped row: one outside the tile or the
   // image is loaded and not used).
   auto centre = [&](FieldRows<MODE, 1>& c, int tb, int k) {
     const int gy = min(max(y0 + tb - 2 * R + C::RG * k + orow, 0), H - 1);
     if constexpr (MODE == kFlowCoarse) {
-      c.issue(0, U, V, a.Hc, a.Wc, ogx, gy);
+      c.template issue<false>(0, U, V, a.Hc, a.Wc, ogx, gy);
     } else if constexpr (MODE == kFlowSame) {
       c.u[0] = U.ld(rowofs(gy, W, ogx), 0);
       c.v[0] = V.ld(rowofs(gy, W, ogx), 0);
@@ -198,16 +218,24 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   const float* win = GAUSS ? pr : hs;
   constexpr int VP = GAUSS ? PP : HP;
   auto solve = [&](int tb, FieldRows<MODE, 1>* c) {
+    // slot of the pass's first output row, tile row tb - R + 1 (its sampled rows start at tb + 2)
+    const int s0 = wrap(ring_row + N);
 #pragma unroll
     for (int k = 0; k < C::K5; ++k) {
       const int r = orow + C::RG * k, j = tb + r - 2 * R;   // row of the pass, of the tile
       if (C::RG * (k + 1) > NR && r >= NR) continue;
       __builtin_amdgcn_sched_barrier(0);   // one round's registers at a time
-      if constexpr (MODE == kFlowCoarse) centre(c[k], tb, k);
+      if constexpr (MODE == kFlowCoarse && !HANDED) centre(c[k], tb, k);
       const int gy = y0 + j;
       const bool out = j >= 0 && j < TH && (INTERIOR || (x0 + oc < W && gy < H));
       const float* s = win + r * VP + oc;
-      const float2 f5 = c[k].at(0, gy, gy);
+      float2 f5;
+      if constexpr (HANDED) {
+        const int q = wrap(s0 + r) * TW + oc;
+        f5 = make_float2(ru[q], rv[q]);
+      } else {
+        f5 = c[k].at(0, gy, gy);
+      }
       float un, vn;
       solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
                    un, vn);
@@ -280,6 +308,19 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     // ------------------------------------------------------------------ P2
     if constexpr (AHEAD) {
       if (more) field(f, yw + NR + F0, g, kRows);
+    }
+    if constexpr (HANDED) {
+      const int c = lx - R - 1;
+      if (c >= 0 && c < TW && gq < G) {
+#pragma unroll
+        for (int k = 0; k < K1; ++k) {
+          if (kLast + k < N || g + k < N) {
+            const int q = wrap(ring_row + g + k) * TW + c;
+            ru[q] = wu[k];
+            rv[q] = wv[k];
+          }
+        }
+      }
     }
     // The products one row above each of this thread's warped rows: the row below is the
     // thread's own, the centre and the row above too from its second and third row on.
@@ -482,6 +523,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     __syncthreads();
     // ------------------------------------------------------------------ P5
     solve(tb, c5);
+    ring_row = wrap(ring_row + N);
     // The next pass's P1 writes warped rows and field rows that this pass's P2 finished reading
     // before the barriers above; its P3 rewrites the window sums after two more barriers.
   }
@@ -491,13 +533,15 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
 }
 
 // True when every position that the tile samples (columns x0-R-1 .. x0+TW+R, rows y0-R-1 .. the
-// last row of the last pass's threads) lies inside the image.
-template <class C>
+// last row of the last pass's threads) lies inside the image, from a coarser level also the rows and
+// columns after those positions' coarse ones.
+template <class C, int MODE>
 __device__ __forceinline__ bool tile_interior(const IterArgs& a, int nbands, int bx, int y0) {
+  constexpr int E = MODE == kFlowCoarse ? 3 : 1;
   constexpr int R = (C::N - 1) / 2;
   const int x0 = bx * C::TW;
   const int last = y0 - R - 1 + C::N * nbands - C::NR + C::P1_FIRST + C::G * C::K1 - 1;
-  return x0 - R - 1 >= 0 && x0 + C::TW + R <= a.W - 1 && y0 - R - 1 >= 0 && last <= a.H - 1;
+  return x0 - R - 1 >= 0 && x0 + C::TW + R <= a.W - E && y0 - R - 1 >= 0 && last <= a.H - E;
 }
 
 // Masked plans: a tile without an unmasked output pixel (TW columns from x0, TH rows from
@@ -542,7 +586,7 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd
     }
     pixel_mask = f == 1;
   }
-  if (tile_interior<Cfg<R, TW, WIDE, BB>>(a, nbands, bx, y0))
+  if (tile_interior<Cfg<R, TW, WIDE, BB>, MODE>(a, nbands, bx, y0))
     strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
   else
     strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
@@ -577,7 +621,7 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>()), (waves_per_simd<
         pixel_mask = f == 1;
       }
     }
-    if (tile_interior<C>(a, nb, w.y, w.z))
+    if (tile_interior<C, MODE>(a, nb, w.y, w.z))
       strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     else
       strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
@@ -646,7 +690,7 @@ template <typename T, int R, int MODE, bool WIDE, bool GAUSS, bool MASK>
 hipError_t go_batch_m(const BatchLaunch& b, hipStream_t s) {
   constexpr int TW = kStripWidth;
   using C = Cfg<R, TW, WIDE>;
-  constexpr size_t kLds = C::LDS_BYTES;
+  constexpr size_t kLds = field_handed<T, R, MODE, GAUSS, false>() ? C::HANDED_LDS_BYTES : C::LDS_BYTES;
   if constexpr (kLds > 65536) {
     static const hipError_t opt = hipFuncSetAttribute(
         reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>),

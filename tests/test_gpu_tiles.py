@@ -136,3 +136,30 @@ def test_gaussian_one_band_tiles(gpu_lib, r, shape):
     plan.set_mask(torch.ones(shape, dtype=torch.uint8, device=dev()))
     assert np.array_equal(flow(1, 1), ref)
     plan.close()
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("r", range(13))
+def test_batch_field_from_coarser_level(gpu_lib, r, f32):
+    """First iterations of a batch, which hand the field of a coarser level on within the tile, against
+    plans, which read it again: the same bits for every radius, odd sizes and tiles of 1 .. 5 bands."""
+    import torch
+    ofmi = gpu_lib
+    announce(f"batch field from the coarser level r={r} f32={f32}")
+    sizes = [(4 * (2 * r + 1) + 3, 201), (max(2 * r + 1, 5), 66), (150, 131)]
+    frames = [[to_dev(np.ascontiguousarray(f[:h, :w])) for f in _frames(150, 201)] for h, w in sizes]
+    if f32:
+        frames = [[f.float() * 0.75 for f in p] for p in frames]
+    b = ofmi.Batch(sizes, 3, r, 1, input_f32=f32, device=dev())
+    for nb in (None, 1, 2, 5):
+        if nb:
+            b.set_config({"bands": [nb] * 3, "variant": [1] * 3, "grid": [0] * 3})
+        us, vs = b.compute([p[0] for p in frames], [p[1] for p in frames])
+        for i, s in enumerate(sizes):
+            plan = ofmi.Plan(*s, 3, r, 1, input_f32=f32, device=dev())
+            u, v = plan.compute(*frames[i])
+            torch.cuda.synchronize()
+            assert torch.equal(u.view(torch.int32), us[i].view(torch.int32)), (nb, i)
+            assert torch.equal(v.view(torch.int32), vs[i].view(torch.int32)), (nb, i)
+            plan.close()
+    b.close()
