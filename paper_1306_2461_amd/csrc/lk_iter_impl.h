@@ -82,10 +82,16 @@ constexpr bool field_handed() {
 // threads, so a tile of two bands (one output band and the band that primes the vertical
 // sums) is one pass of the dependent path instead of two; P4 walks the two bands in order,
 // with the same additions as two single-band passes.  nbands is then even.
+// ONE (BB = 2): the tile is one pass (one output band).  Nothing is carried to a next pass (17
+// registers at r = 8, which the launches from a coarser level otherwise spill), P4 forms only the rows
+// that are output and P5 is a single round: r = 8, iterations of a 512^2 level on 32 columns 8.4 -> 7.8 us,
+// of a 256^2 level on 16 columns 5.3 -> 5.1 us.
 template <typename T, int R, int TW, int MODE, bool WIDE, bool INTERIOR, bool GAUSS, int BB,
-          bool BUB>
-__device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands, int bx, int y0,
+          bool BUB, bool ONE>
+__device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands, int bx, int y0,
                                            bool pixel_mask, float4* sm4) {
+  static_assert(!ONE || BB == 2, "one pass: both of its bands");
+  const int nbands = ONE ? BB : bands;
   using C = Cfg<R, TW, WIDE, BB>;
   constexpr int N = C::N, NR = C::NR, NT = C::NT, PC = C::PC, WC = C::WC, PP = C::PP, WP = C::WP,
                 HP = C::HP, K1 = C::K1, G = C::G, F0 = C::P1_FIRST;
@@ -199,10 +205,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
   constexpr int RING = C::RING;
   int ring_row = 0;
   auto wrap = [](int s) { return s >= RING ? s - RING : s; };
+  // Rows of a pass that P5 visits, and its rounds.
+  constexpr int R5 = ONE ? 2 * R : 0, N5 = ONE ? N : NR, K5 = (N5 + C::RG - 1) / C::RG;
   // Field at this thread's output pixel of round k (clamped row: one outside the tile or the
   // image is loaded and not used).
   auto centre = [&](FieldRows<MODE, 1>& c, int tb, int k) {
-    const int gy = min(max(y0 + tb - 2 * R + C::RG * k + orow, 0), H - 1);
+    const int gy = min(max(y0 + tb - 2 * R + R5 + C::RG * k + orow, 0), H - 1);
     if constexpr (MODE == kFlowCoarse) {
       c.template issue<false>(0, U, V, a.Hc, a.Wc, ogx, gy);
     } else if constexpr (MODE == kFlowSame) {
@@ -221,24 +229,27 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     // slot of the pass's first output row, tile row tb - R + 1 (its sampled rows start at tb + 2)
     const int s0 = wrap(ring_row + N);
 #pragma unroll
-    for (int k = 0; k < C::K5; ++k) {
-      const int r = orow + C::RG * k, j = tb + r - 2 * R;   // row of the pass, of the tile
-      if (C::RG * (k + 1) > NR && r >= NR) continue;
+    for (int k = 0; k < K5; ++k) {
+      const int r = R5 + orow + C::RG * k, j = tb + r - 2 * R;   // row of the pass, of the tile
+      if (C::RG * (k + 1) > N5 && r >= R5 + N5) continue;
       __builtin_amdgcn_sched_barrier(0);   // one round's registers at a time
       if constexpr (MODE == kFlowCoarse && !HANDED) centre(c[k], tb, k);
       const int gy = y0 + j;
       const bool out = j >= 0 && j < TH && (INTERIOR || (x0 + oc < W && gy < H));
-      const float* s = win + r * VP + oc;
-      float2 f5;
-      if constexpr (HANDED) {
-        const int q = wrap(s0 + r) * TW + oc;
-        f5 = make_float2(ru[q], rv[q]);
-      } else {
-        f5 = c[k].at(0, gy, gy);
+      float un = 0.f, vn = 0.f;
+      // (a row above the tile: of its first band, uniform over a wave on 64-column strips)
+      if (TW != 64 || j >= 0) {
+        const float* s = win + r * VP + oc;
+        float2 f5;
+        if constexpr (HANDED) {
+          const int q = wrap(s0 + r) * TW + oc;
+          f5 = make_float2(ru[q], rv[q]);
+        } else {
+          f5 = c[k].at(0, gy, gy);
+        }
+        solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
+                     un, vn);
       }
-      float un, vn;
-      solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
-                   un, vn);
       const unsigned o = rowofs(gy, W, x0 + oc);
       if (pixel_mask) {   // masked-out pixels: zero flow
         if (out && at(a.mask, o) == 0) un = vn = 0.f;
@@ -446,10 +457,10 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
     }
     __syncthreads();
     // ------------------------------------------------------------------ P4
-    FieldRows<MODE, 1> c5[C::K5];
+    FieldRows<MODE, 1> c5[K5];
     if constexpr (AHEAD) {
 #pragma unroll
-      for (int k = 0; k < C::K5; ++k) centre(c5[k], tb, k);
+      for (int k = 0; k < K5; ++k) centre(c5[k], tb, k);
     }
     if (GAUSS && BB == 2 && p4) {
       // A tile of one pass: its output rows 2R .. 4R have their whole windows in the pass, M rows
@@ -508,6 +519,17 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
 #pragma unroll
         for (int r = 0; r < N; ++r) cur[r] = col[r * HP];
         __builtin_amdgcn_sched_barrier(0);
+        // A tile's first band outputs its last row (with P5's skipped rows: 2048^2 level 0 at 8
+        // bands 32.2 -> 31.7 us, 1024^2 at 2 bands 13.9 -> 13.6 us).
+        if (BB == 1 && b == 0) {
+          float s = cur[0];
+#pragma unroll
+          for (int r = 1; r < N; ++r) s += cur[r];
+          col[(N - 1) * HP] = s;
+#pragma unroll
+          for (int r = 0; r < N; ++r) prev[r] = cur[r];
+          continue;
+        }
         // prev[r] <- prev[r] + ... + prev[N-1] (suffix sums of the previous band, in place)
 #pragma unroll
         for (int r = N - 2; r >= 0; --r) prev[r] += prev[r + 1];
@@ -515,7 +537,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int nbands
 #pragma unroll
         for (int r = 0; r < N; ++r) {
           pre = r == 0 ? cur[r] : pre + cur[r];
-          col[r * HP] = r + 1 < N ? prev[r + 1] + pre : pre;
+          if (!ONE || bb == 1 || r + 1 == N) col[r * HP] = r + 1 < N ? prev[r + 1] + pre : pre;
           prev[r] = cur[r];
         }
       }
@@ -569,7 +591,7 @@ __device__ __forceinline__ int xcd_order(int b, int nblocks) {
   return (b % kXcd) * per + b / kXcd;
 }
 
-template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, int BB>
+template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, int BB, bool ONE>
 __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd<R, TW, WIDE, BB>())) void lk_iter_strip(IterArgs a, int TH,
                                                                            int nbands, int tiles_x,
                                                                            int ntiles) {
@@ -587,9 +609,9 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd
     pixel_mask = f == 1;
   }
   if (tile_interior<Cfg<R, TW, WIDE, BB>, MODE>(a, nbands, bx, y0))
-    strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
+    strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
   else
-    strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, BB, true>(a, TH, nbands, bx, y0, pixel_mask, sm4);
+    strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
 }
 
 // Batched form: workgroups stride over a work list of tiles of many pairs at the same
@@ -622,16 +644,16 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>()), (waves_per_simd<
       }
     }
     if (tile_interior<C, MODE>(a, nb, w.y, w.z))
-      strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
+      strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     else
-      strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, 1, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
+      strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     __syncthreads();
   }
 }
 
 // nb output bands per tile take nb + 1 bands (the first primes the vertical sums), rounded up
 // to whole passes of BB bands (a band past the tile's rows writes nothing).
-template <typename T, int R, int MODE, bool WIDE, bool GAUSS, int TWV = 0, int BB = 1>
+template <typename T, int R, int MODE, bool WIDE, bool GAUSS, int TWV = 0, int BB = 1, bool ONE = false>
 hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   constexpr int TW = TWV ? TWV : kStripWidth;
   using C = Cfg<R, TW, WIDE, BB>;
@@ -645,11 +667,11 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   if constexpr (kLds > 65536) {
     // Opt in to more than 64 KB of dynamic LDS (gfx950 has 160 KB per workgroup), once.
     static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB>),
+        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB, ONE>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (opt != hipSuccess) return opt;
   }
-  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB>), dim3(grid),
+  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB, ONE>), dim3(grid),
                      dim3(C::NT), kLds, s, a, TH, nbands, tx, ntiles);
   return hipGetLastError();
 }
@@ -668,12 +690,14 @@ hipError_t go_plain_g(const IterArgs& a, int nb, int variant, hipStream_t s) {
     }
   }
   if constexpr (R <= kMaxPairRadius) {   // two bands per pass (Gaussian: tiles of one pass)
-    if (!GAUSS || nb == 1) {
-      switch (variant) {
-        case kTileWide32x2:
-        case kTileLean32x2: return go_plain_v<T, R, MODE, true, GAUSS, 32, 2>(a, nb, s);
-        case kTileWide16x2: return go_plain_v<T, R, MODE, true, GAUSS, 16, 2>(a, nb, s);
-      }
+    const bool w32 = variant == kTileWide32x2 || variant == kTileLean32x2;
+    if (w32 || variant == kTileWide16x2) {
+      if (nb == 1)
+        return w32 ? go_plain_v<T, R, MODE, true, GAUSS, 32, 2, true>(a, nb, s)
+                   : go_plain_v<T, R, MODE, true, GAUSS, 16, 2, true>(a, nb, s);
+      if constexpr (!GAUSS)
+        return w32 ? go_plain_v<T, R, MODE, true, false, 32, 2>(a, nb, s)
+                   : go_plain_v<T, R, MODE, true, false, 16, 2>(a, nb, s);
     }
   }
   return hipErrorInvalidValue;
