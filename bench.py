@@ -42,6 +42,7 @@ PROBE_BATCH_CONFIG = {"bands": [16, 8, 2, 1], "grid": [2048, 512, 1024, 512], "v
 # Sources of the fused iteration kernel: the HBM traffic recorded in the counter summary is
 # used only while they are unchanged.
 KERNEL_SOURCES = ["paper_1306_2461_amd/csrc/lk_iter_impl.h", "paper_1306_2461_amd/csrc/common.h",
+                  "paper_1306_2461_amd/csrc/lk_iter_cfg.h", "paper_1306_2461_amd/csrc/lk_iter_inst.hip",
                   "paper_1306_2461_amd/csrc/lk_iter.hip", "paper_1306_2461_amd/csrc/kernels.h"]
 COUNTER_SUMMARY = "profiles/lk_iter_1024_plain_path_counters.md"
 
