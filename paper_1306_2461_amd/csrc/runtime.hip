@@ -60,6 +60,12 @@ double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gau
   // cost of the launch and a tile's ends, and of a band, by strip width and bands per pass
   double base = sh.bb == 2 || sh.tw == 32 ? 1.5 : (sh.tw == 16 ? 1.0 : 2.0);
   double band = sh.bb == 2 ? (sh.tw == 16 ? 0.58 : 0.75) : (sh.tw == 16 ? 0.85 : (sh.tw == 32 ? 0.9 : 1.0));
+  // One-pass tiles form the output rows only, and up to r = 4 their 64 registers let 32 waves share
+  // a CU (r = 4, 512^2: 7.6 us at two bands in 64-column strips, 6.8 us so; r = 2, 320^2: 5.9 us in
+  // 32-column strips, 5.2 us so).
+  const bool one = sh.bb == 2 && nb == 1;
+  const int per_cu = one && !gauss && R <= 4 ? 2048 / sh.threads : sh.per_cu;
+  if (one) band *= 0.9;
   if (gauss) {
     base = R > 2 ? 5.0 / R : 2.0;
     band = sh.bb == 2 ? std::min(0.8, sh.tw == 16 ? 0.98 - 0.0575 * R : 1.1 - 0.06 * R) : 1.0;
@@ -76,7 +82,7 @@ double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gau
   auto shared = [&](long long t) {   // slow-down of t tiles spread over the CUs
     return 1.0 + 0.6 * ((t + kCus - 1) / kCus - 1) * sh.threads / 768.0;
   };
-  const long long slots = (long long)kCus * sh.per_cu, full = tiles / slots, rest = tiles % slots;
+  const long long slots = (long long)kCus * per_cu, full = tiles / slots, rest = tiles % slots;
   double t;
   if (full < 3)
     t = full * shared(slots) * tall + (rest ? shared(rest) * tall : 0.0);
