@@ -35,8 +35,9 @@
 // variants that kept more in flight (samples gathered a band ahead) spilled or fell to one
 // workgroup per CU and were slower.  Measured on level 0 of 16 pairs of 1024^2 (r = 8, uint8, tiles
 // of 16 bands, iterations of a level averaged): 139.8 us per launch before the per-column mapping,
-// 8-bit samples and paired coarse rows below, 119.5 us with them (16.8 Mpx: 2.5 TB/s of algorithmic
-// bytes); a plan's 2048^2 level 0 (8 bands) 42.9 -> 32.1 us.  Vector memory instructions cost by
+// 8-bit samples and paired coarse rows below, 119.5 us with them, 113 us with the field handed on and
+// the first band's unused rows left out (16.8 Mpx: 2.7 TB/s of algorithmic bytes); a plan's 2048^2
+// level 0 (8 bands) 42.9 -> 31.7 us.  Vector memory instructions cost by
 // form, not by bytes: 64 lanes at unit stride 4.7 clocks per CU (bytes or dwords), 64-bit, stride-2
 // or unaligned 16-bit lanes 16 clocks, so every load and store here is one element per lane at unit
 // stride and a bilinear tap pair is two byte loads.
