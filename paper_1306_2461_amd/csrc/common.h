@@ -207,29 +207,44 @@ struct Sample<uint8_t> {
 template <int MODE, int K>
 struct FieldRows {   // the previous iteration at the same level
   float u[K], v[K];
-  __device__ __forceinline__ float2 at(int k, int, int) const { return make_float2(u[k], v[k]); }
+  template <bool INTERIOR>
+  __device__ __forceinline__ float2 at(int k, int, int, bool) const { return make_float2(u[k], v[k]); }
 };
 template <int K>
 struct FieldRows<kFlowZero, K> {
-  __device__ __forceinline__ float2 at(int, int, int) const { return make_float2(0.f, 0.f); }
+  template <bool INTERIOR>
+  __device__ __forceinline__ float2 at(int, int, int, bool) const { return make_float2(0.f, 0.f); }
 };
 // The coarser level's Hc x Wc field: 2 * bilinear(coarse, x/2, y/2) at in-image pixel (x, y), base
-// floor(x/2), floor(y/2), fractions 0 or 1/2.  Two successive rows lie between the same two rows
-// of the coarser level (an even second row on the lower of them), so a pair takes eight loads.
+// floor(x/2), floor(y/2), fractions 0 or 1/2: every row reads its base row and the row after it, also
+// where the fraction is 0 (a field that is not finite there must not depend on how rows are dealt to
+// threads).  Two successive rows share two rows of the coarser level; an even second row lies one
+// further down and also takes the row after the pair's, which the next pair has loaded, or TAIL does
+// for the last pair of an even K.  (Without that row, an even second row's value being its base row
+// alone, a pair of 2048^2 took 236.0 instead of 238.7 us and 16 pairs of 1024^2 702.7 instead of 708.0,
+// but what a NaN or an infinity of a float frame reached followed from the tiles.  Its loads under a
+// branch on the parity spill: 713.6 us.)
 template <int K>
 struct FieldRows<kFlowCoarse, K> {
   static constexpr int NP = (K + 1) / 2;
+  static constexpr bool TAIL = K % 2 == 0;
   float u00[NP], u01[NP], u10[NP], u11[NP], v00[NP], v01[NP], v10[NP], v11[NP], fa;
-  // Pair p, whose first row is y.  INTERIOR: the coarse row and column after the base exist.
+  float u20, u21, v20, v21;   // TAIL
+  // Pair p, whose first row is y.  INTERIOR: the coarse row and column after every row's base exist.
   template <bool INTERIOR>
   __device__ __forceinline__ void issue(int p, const Plane<float>& U, const Plane<float>& V, int Hc, int Wc, int x,
                                         int y) {
     const int x0 = x >> 1, y0 = y >> 1;
     fa = (x & 1) ? 0.5f : 0.f;
+    const bool tail = TAIL && p == NP - 1;
     if constexpr (INTERIOR) {
       const unsigned o = rowofs(y0, Wc, x0);
       u00[p] = U.ld(o, 0), u01[p] = U.ld(o + 1u, 0), u10[p] = U.ld(o, Wc), u11[p] = U.ld(o + 1u, Wc);
       v00[p] = V.ld(o, 0), v01[p] = V.ld(o + 1u, 0), v10[p] = V.ld(o, Wc), v11[p] = V.ld(o + 1u, Wc);
+      if (tail) {
+        u20 = U.ld(o, 2 * Wc), u21 = U.ld(o + 1u, 2 * Wc);
+        v20 = V.ld(o, 2 * Wc), v21 = V.ld(o + 1u, 2 * Wc);
+      }
       return;
     }
     const unsigned dx = x0 < Wc - 1 ? 1u : 0u;
@@ -238,19 +253,30 @@ struct FieldRows<kFlowCoarse, K> {
     const unsigned i01 = i00 + dx, i10 = i00 + dy, i11 = i00 + dy + dx;
     u00[p] = U.ld(i00, 0), u01[p] = U.ld(i01, 0), u10[p] = U.ld(i10, 0), u11[p] = U.ld(i11, 0);
     v00[p] = V.ld(i00, 0), v01[p] = V.ld(i01, 0), v10[p] = V.ld(i10, 0), v11[p] = V.ld(i11, 0);
+    if (tail) {
+      const unsigned i20 = rowofs(min(y0 + 2, Hc - 1), Wc, x0), i21 = i20 + dx;
+      u20 = U.ld(i20, 0), u21 = U.ld(i21, 0), v20 = V.ld(i20, 0), v21 = V.ld(i21, 0);
+    }
   }
-  __device__ __forceinline__ float value(float z00, float z01, float z10, float z11, bool lower, float fb) const {
-    const float t = fmaf(fa, z01 - z00, z00);
-    const float s = fmaf(fa, z11 - z10, z10);
-    return 2.f * (lower ? s : fmaf(fb, s - t, t));
-  }
-  // Row k, at image row y; ya: the first row of its pair.
-  __device__ __forceinline__ float2 at(int k, int y, int ya) const {
+  __device__ __forceinline__ float across(float z0, float z1) const { return fmaf(fa, z1 - z0, z0); }
+  // Row k, at image row y; ya: the first row of its pair.  With even K the threads' first rows share
+  // one parity, y0_odd, which decides in tiles without clamps (INTERIOR).
+  template <bool INTERIOR>
+  __device__ __forceinline__ float2 at(int k, int y, int ya, bool y0_odd) const {
+    constexpr bool UNI = INTERIOR && TAIL;
     const int p = k / 2;
-    const bool lower = (y >> 1) != (ya >> 1);
-    const float fb = (y & 1) ? 0.5f : 0.f;
-    return make_float2(value(u00[p], u01[p], u10[p], u11[p], lower, fb),
-                       value(v00[p], v01[p], v10[p], v11[p], lower, fb));
+    const float fb = (UNI ? y0_odd != (k % 2 == 1) : (y & 1) != 0) ? 0.5f : 0.f;
+    float tu = across(u00[p], u01[p]), tv = across(v00[p], v01[p]);
+    float su = across(u10[p], u11[p]), sv = across(v10[p], v11[p]);
+    if (k % 2 == 1) {
+      const bool lower = UNI ? y0_odd : (y >> 1) != (ya >> 1);
+      const int n = p + 1 < NP ? p + 1 : p;
+      const float nu = p + 1 < NP ? across(u10[n], u11[n]) : across(u20, u21);
+      const float nv = p + 1 < NP ? across(v10[n], v11[n]) : across(v20, v21);
+      tu = lower ? su : tu, tv = lower ? sv : tv;
+      su = lower ? nu : su, sv = lower ? nv : sv;
+    }
+    return make_float2(2.f * fmaf(fb, su - tu, tu), 2.f * fmaf(fb, sv - tv, tv));
   }
 };
 

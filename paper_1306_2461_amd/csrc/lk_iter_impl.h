@@ -153,7 +153,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
     }
   };
   auto field_at = [&](const auto& f, int ys, int i, int k) {
-    return f.at(k, row_at(ys + k, i), row_at(ys + k / 2 * 2, i));
+    return f.template at<INTERIOR>(k, row_at(ys + k, i), row_at(ys + k / 2 * 2, i), ys & 1);
   };
   // Frame 1 one row above this thread's k-th row of the pass whose LDS row 0 is image row yw.
   auto frame1 = [&](int yw, int k) {
@@ -246,7 +246,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
           const int q = wrap(s0 + r) * TW + oc;
           f5 = make_float2(ru[q], rv[q]);
         } else {
-          f5 = c[k].at(0, gy, gy);
+          f5 = c[k].template at<false>(0, gy, gy, false);
         }
         solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
                      un, vn);
