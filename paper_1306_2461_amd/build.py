@@ -18,7 +18,7 @@ LIB = os.path.join(LIBDIR, "libofmi.so")
 # (kRadiusGroups) are translation units of their own, the longest first.
 SOURCES = [("lk_iter_inst.hip", f"lk_iter_{t}_{g}", [f"-DOFMI_ITER_ELEM={t}", f"-DOFMI_ITER_GROUP={g}"])
            for g in (0, 1, 2, 3, 4) for t in ("u8", "f32", "f16")]
-SOURCES += [(s + ".hip", s, []) for s in ("lk_iter", "pyramid", "runtime", "batch", "serve", "extras")]
+SOURCES += [(s + ".hip", s, []) for s in ("lk_iter", "tiles", "pyramid", "runtime", "batch", "serve", "extras")]
 
 # Packed FP32 arithmetic is disabled for every HIP translation unit.
 HIPFLAGS = [

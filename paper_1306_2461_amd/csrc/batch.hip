@@ -9,7 +9,9 @@
 #include <string.h>
 
 #include <algorithm>
+#include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/ofmi.h"
@@ -117,11 +119,13 @@ bool check_batch(int n, const int* H, const int* W, int levels, int radius, int 
 }
 
 int default_batch_bands(const of_batch* b, int l) {
+  std::map<std::pair<int, int>, int> sizes;   // batches hold few distinct ones
+  for (const Geometry& g : b->g) ++sizes[{g.H[l], g.W[l]}];
   std::vector<PlaneSize> s;
-  for (const Geometry& g : b->g) s.push_back({g.H[l], g.W[l]});
-  int cand[32];
-  for (int i = 0; i < 32; ++i) cand[i] = i + 1;
-  return best_bands(s.data(), b->n, b->R, kTileWide, cand, 32);
+  for (const auto& [hw, n] : sizes) s.push_back({hw.first, hw.second, n});
+  int cand[LaunchCost::kMostBands];
+  for (int i = 0; i < LaunchCost::kMostBands; ++i) cand[i] = i + 1;
+  return best_bands(s.data(), (int)s.size(), b->R, cand, LaunchCost::kMostBands);
 }
 
 // Work items one pair's level can need at any tile height: the one-band tiles, or at taller
@@ -402,17 +406,19 @@ size_t of_batch_workspace_bytes(int n, const int* H, const int* W, int levels, i
                                 int iters, unsigned flags) {
   if (!check_batch(n, H, W, levels, radius, iters, flags)) return 0;
   size_t off = 0, tiles = 0, items = 0;
+  size_t tl[OF_MAX_LEVELS] = {}, it[OF_MAX_LEVELS] = {};
   const int N = 2 * radius + 1, TW = strip_width_for(radius);
-  for (int l = 0; l < levels; ++l) {
-    size_t tl = 0, it = 0;
-    for (int p = 0; p < n; ++p) {
-      Geometry g = make_geometry(H[p], W[p], levels, radius, iters, flags);
-      if (l == 0) off += align256(g.bytes);
-      tl += list_capacity(g.H[l], g.W[l], N, TW);
-      if (l >= 1) it += 2 * (size_t)reduce_blocks(g.elem(l - 1), g.H[l], g.W[l]);
+  for (int p = 0; p < n; ++p) {
+    const Geometry g = make_geometry(H[p], W[p], levels, radius, iters, flags);
+    off += align256(g.bytes);
+    for (int l = 0; l < levels; ++l) {
+      tl[l] += list_capacity(g.H[l], g.W[l], N, TW);
+      if (l >= 1) it[l] += 2 * (size_t)reduce_blocks(g.elem(l - 1), g.H[l], g.W[l]);
     }
-    tiles = std::max(tiles, tl);
-    items += align256(it * sizeof(int2));
+  }
+  for (int l = 0; l < levels; ++l) {
+    tiles = std::max(tiles, tl[l]);
+    items += align256(it[l] * sizeof(int2));
   }
   return off + align256(tiles * sizeof(int4)) * levels + items + kArgSlots * args_bytes(n, levels, iters);
 }

@@ -5,6 +5,7 @@
 #include <stddef.h>
 
 #include "common.h"
+#include "tiles.h"
 
 namespace ofmi {
 
@@ -51,25 +52,6 @@ hipError_t launch_reduce_chain(Elem tin, Elem tout, const ReduceChain& c, hipStr
 hipError_t launch_reduce(Elem tin, Elem tout, const void* in1, const void* in2, int H, int W,
                          void* out1, void* out2, int Ho, int Wo, hipStream_t s);
 
-// Tile variants of the iteration kernel:
-//   narrow     64-column strips, 5 threads per output column;
-//   wide       64-column strips, about 12 threads per output column;
-//   wide 32 /  the wide variant on strips of 32 or 16 output columns (plain launches of the
-//   wide 16    box window): small levels spread over more CUs, hence a shorter path per band
-//              where a level has fewer tiles than CUs.
-//   wide 32x2 / the same strips with two bands per pass (plain launches, r <= kMaxPairRadius; for
-//   wide 16x2   the Gaussian window chosen by the host for tiles of one output band): a tile of one output band runs its priming band and its
-//              output band together, one dependent path.
-//   wide lean, lean 32x2: the kernels of wide and wide 32x2 (kept as configuration values).
-enum TileVariant : int { kTileNarrow = 0, kTileWide = 1, kTileWideLean = 2, kTileWide32 = 3,
-                         kTileWide16 = 4, kTileWide32x2 = 5, kTileWide16x2 = 6, kTileLean32x2 = 7 };
-constexpr int kTileVariants = 8;
-// Largest window radius of the two-bands-per-pass variants (two workgroups share a CU's
-// LDS).
-constexpr int kMaxPairRadius = 8;
-// Added to a plain launch's variant: Gaussian-weighted window sums (taps in IterArgs::taps).
-constexpr int kTileGauss = 16;
-
 // Batched iteration launch: `grid` workgroups stride over `ntiles` work items (pair | tile
 // flag << 16, tile x, first output row, output rows) with per-pair arguments args[pair]
 // (device arrays); the flag (0 no unmasked pixel, 1 some masked pixels, 2 none) is read for
@@ -86,32 +68,6 @@ struct BatchLaunch {
   // ahead instead of paying on a request).
   bool prime = false;
 };
-
-// Workgroup of a tile variant at radius R: output columns, bands per pass, threads, workgroups
-// that share a CU.
-struct TileShape {
-  int tw, bb, threads, per_cu;
-};
-TileShape tile_shape(int variant, int R);
-// Strip width (output columns per tile) of the iteration kernel for radius R (variants 0-2).
-int strip_width_for(int R);
-// Strip width of a plain launch's tile variant.
-inline int tile_width(int variant, int R) {
-  if (variant == kTileWide32 || variant == kTileWide32x2 || variant == kTileLean32x2) return 32;
-  if (variant == kTileWide16 || variant == kTileWide16x2) return 16;
-  return strip_width_for(R);
-}
-// Whether a plain launch of radius R (Gaussian-weighted window or not) has tile variant
-// `variant`: narrow strips only with the box window, two bands per pass only up to
-// kMaxPairRadius.
-inline bool tile_variant_valid(int variant, int R, bool gaussian) {
-  if (variant < kTileNarrow || variant >= kTileVariants) return false;
-  if (gaussian && variant > kTileWideLean) return false;
-  if ((variant == kTileWide32x2 || variant == kTileWide16x2 || variant == kTileLean32x2) &&
-      R > kMaxPairRadius)
-    return false;
-  return true;
-}
 
 // The iteration kernel's translation units: one per frame type and range of radii
 // [kRadiusGroups[g], kRadiusGroups[g+1]).

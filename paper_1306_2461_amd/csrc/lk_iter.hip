@@ -3,7 +3,6 @@
 #include <cstdint>
 
 #include "kernels.h"
-#include "lk_iter_cfg.h"
 
 namespace ofmi {
 
@@ -17,51 +16,6 @@ namespace ofmi {
 OFMI_DECLARE_ELEM(uint8_t)
 OFMI_DECLARE_ELEM(float)
 OFMI_DECLARE_ELEM(__half)
-
-namespace {
-
-template <int R, int TW, bool WIDE, int BB>
-constexpr TileShape shape() {
-  using C = Cfg<R, TW, WIDE, BB>;
-  // workgroups per CU: 24 waves of 80 registers where the kernel is compiled for two, 160 KB LDS
-  const int by_waves = waves_per_simd<R, TW, WIDE, BB>() > 1 ? 24 / ((C::NT + 63) / 64) : 1;
-  const int by_lds = (int)(160 * 1024 / C::LDS_BYTES);
-  const int n = by_waves < by_lds ? by_waves : by_lds;
-  return {TW, BB, C::NT, n < 1 ? 1 : n};
-}
-
-template <int R>
-TileShape shape_r(int variant) {
-  switch (variant) {
-    case kTileNarrow: return shape<R, kStripWidth, false, 1>();
-    case kTileWide32: return shape<R, 32, true, 1>();
-    case kTileWide16: return shape<R, 16, true, 1>();
-  }
-  if constexpr (R <= kMaxPairRadius) {
-    switch (variant) {
-      case kTileWide32x2:
-      case kTileLean32x2: return shape<R, 32, true, 2>();
-      case kTileWide16x2: return shape<R, 16, true, 2>();
-    }
-  }
-  return shape<R, kStripWidth, true, 1>();
-}
-
-template <int R = 0>
-TileShape shape_any(int R_, int variant) {
-  if (R_ == R) return shape_r<R>(variant);
-  if constexpr (R < 12) return shape_any<R + 1>(R_, variant);
-  return {};
-}
-
-}  // namespace
-
-TileShape tile_shape(int variant, int R) { return shape_any(R, variant); }
-
-int strip_width_for(int R) {
-  (void)R;   // every supported radius
-  return kStripWidth;
-}
 
 namespace {
 

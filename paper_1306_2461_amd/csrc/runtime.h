@@ -23,6 +23,7 @@ struct Geometry {
   size_t off_p1[OF_MAX_LEVELS];     // workspace offsets of the pyramid levels (>= 1)
   size_t off_p2[OF_MAX_LEVELS];
   size_t off_flow[4];               // ping-pong u0, u1, v0, v1 (level-0 size each)
+  // plans only (batches and sessions choose theirs for all pairs of a launch):
   int nb[OF_MAX_LEVELS];            // iteration tile height per level, in bands of 2R+1 rows
   int variant[OF_MAX_LEVELS];       // tile variant of the iteration kernel (TileVariant)
   int one_band[OF_MAX_LEVELS];      // Gaussian window, tiles of one output band: variant that runs them
@@ -142,16 +143,8 @@ std::vector<uint8_t> tile_flags(const uint8_t* mask, int H, int W, int TW, int T
 // the tile's first to its last band that holds an unmasked pixel; the band boundaries stay
 // where the tile's are, so the window sums round as in the uncut tile.
 void band_cut(const uint8_t* m, int W, int c0, int c1, int y0, int e, int N, int& ty0, int& th);
-// Size of one pair's plane at a level.
-struct PlaneSize {
-  int H, W;
-};
-// Estimated time of one iteration launch over n planes with tile variant `variant` and tiles of nb
-// bands, in units of one band of a lone wide tile (see the definition).
-double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gauss);
-// The tile height of least estimated cost among `cand`.
-int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, int ncand);
 bool check_params(int H, int W, int levels, int radius, int iters, unsigned flags);
+// Sizes and workspace offsets (without tiles, which plans add).
 Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned flags);
 hipError_t enqueue_pair(const Geometry& g, char* ws, const void* I1, const void* I2, float* u,
                         float* v, hipStream_t s, KernelTimer* t);

@@ -37,73 +37,6 @@ bool check_params(int H, int W, int levels, int radius, int iters, unsigned flag
   return true;
 }
 
-// A launch's time by its tiles, fitted to event timings of every variant and tile height at r = 2, 4,
-// 8, 10 on levels of 200^2 .. 2048^2 and on 16 pairs of 1024^2 (it ranks the heights as measured, or
-// picks one within a few per cent).  A tile of nb output bands walks nb + 1 (the first primes the
-// vertical sums) and costs a quarter band to start.  A band takes one unit on a CU of its own; k
-// workgroups of t threads sharing the CU slow each other to 1 + 0.6 (k-1) t/768 (r = 8: 2.03 us
-// alone, 3.3 us in twos).  Tiles beyond what the 256 CUs hold at once run in further rounds; many
-// rounds even out, and only the total and a part of a last tile count.  Examples (r = 8, measured /
-// model): 2048^2 at 8 bands 32.9 us / 16.8, 4 bands 36.3 / 18.8, 16 bands 42.1 / 19.3; 1024^2 at 2
-// bands 14.4 / 7.2, 3 bands 16.6 / 8.8, 4 bands 15.0 / 7.3; 16 x 1024^2 at 31 bands 123, 16 bands 123,
-// 8 bands 128, 4 bands 149, 2 bands 168 us.
-// The Gaussian-weighted window's bands take longer (2 (2r+1) multiply-adds per product and sum),
-// those of a two-band pass less so, as its vertical sums spread over all threads.  Fitted at r = 4
-// and 8 on levels of 64^2 .. 1024^2, e.g. r = 8 (measured / model): 128^2 at one band in 64-column
-// strips 9.5 us / 2.9, two-band passes on 32 columns 6.3 / 2.0, on 16 columns 5.7 / 1.8; 512^2 9.8 /
-// 2.9, 9.1 / 2.8, 11.4 / 4.4; 1024^2 23.7 / 7.8, 24.9 / 8.6, 34.8 / 14, at two bands in 64-column
-// strips 19.2 / 5.8.
-double iter_cost(const PlaneSize* s, int n, int R, int variant, int nb, bool gauss) {
-  constexpr int kCus = 256;
-  const TileShape sh = tile_shape(variant, R);
-  const int N = 2 * R + 1;
-  // cost of the launch and a tile's ends, and of a band, by strip width and bands per pass
-  double base = sh.bb == 2 || sh.tw == 32 ? 1.5 : (sh.tw == 16 ? 1.0 : 2.0);
-  double band = sh.bb == 2 ? (sh.tw == 16 ? 0.58 : 0.75) : (sh.tw == 16 ? 0.85 : (sh.tw == 32 ? 0.9 : 1.0));
-  // One-pass tiles form the output rows only, and up to r = 4 their 64 registers let 32 waves share
-  // a CU (r = 4, 512^2: 7.6 us at two bands in 64-column strips, 6.8 us so; r = 2, 320^2: 5.9 us in
-  // 32-column strips, 5.2 us so).
-  const bool one = sh.bb == 2 && nb == 1;
-  const int per_cu = one && !gauss && R <= 4 ? 2048 / sh.threads : sh.per_cu;
-  if (one) band *= 0.9;
-  if (gauss) {
-    base = R > 2 ? 5.0 / R : 2.0;
-    band = sh.bb == 2 ? std::min(0.8, sh.tw == 16 ? 0.98 - 0.0575 * R : 1.1 - 0.06 * R) : 1.0;
-  }
-  long long tiles = 0;
-  double work = 0, tall = 0;
-  for (int i = 0; i < n; ++i) {
-    const int bands = (s[i].H + N - 1) / N, h = std::min(nb, bands);
-    const long long tx = (s[i].W + sh.tw - 1) / sh.tw, ty = (bands + nb - 1) / nb;
-    tiles += tx * ty;
-    work += tx * (bands + 1.25 * ty);
-    tall = std::max(tall, (h + 1 + sh.bb - 1) / sh.bb * sh.bb + 0.25);
-  }
-  auto shared = [&](long long t) {   // slow-down of t tiles spread over the CUs
-    return 1.0 + 0.6 * ((t + kCus - 1) / kCus - 1) * sh.threads / 768.0;
-  };
-  const long long slots = (long long)kCus * per_cu, full = tiles / slots, rest = tiles % slots;
-  double t;
-  if (full < 3)
-    t = full * shared(slots) * tall + (rest ? shared(rest) * tall : 0.0);
-  else
-    t = shared(slots) * (work / slots + (rest ? 0.25 * tall : 0.0));
-  return base + band * t;
-}
-
-int best_bands(const PlaneSize* s, int n, int R, int variant, const int* cand, int ncand) {
-  int best = cand[0];
-  double cost = 1e300;
-  for (int i = 0; i < ncand; ++i) {
-    const double c = iter_cost(s, n, R, variant, cand[i], false);
-    if (c < cost) {
-      cost = c;
-      best = cand[i];
-    }
-  }
-  return best;
-}
-
 Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned flags) {
   Geometry g{};
   g.L = levels;
@@ -115,48 +48,6 @@ Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned
   for (int l = 1; l < levels; ++l) {
     g.H[l] = (g.H[l - 1] + 1) / 2;
     g.W[l] = (g.W[l - 1] + 1) / 2;
-  }
-  for (int l = 0; l < levels; ++l) {
-    // Variant and tile height of least estimated cost: 64-column strips, with the box window also
-    // strips of 32 columns (r <= 3, whose bands are short, and r > 8, which has no two-band
-    // passes) or 16 (r > 8) and two bands per pass (r <= 8; whole passes: an odd height).
-    const bool box = !(flags & OF_FLAG_GAUSSIAN_WINDOW);
-    const PlaneSize s = {g.H[l], g.W[l]};
-    double cost = 1e300;
-    auto consider = [&](int variant, int step) {
-      for (int nb = 1; nb <= 32; nb += step) {
-        const double c = iter_cost(&s, 1, radius, variant, nb, !box);
-        if (c < cost) {
-          cost = c;
-          g.variant[l] = variant;
-          g.nb[l] = nb;
-        }
-      }
-    };
-    consider(kTileWide, 1);
-    if (box && (radius <= 3 || radius > kMaxPairRadius)) consider(kTileWide32, 1);
-    if (box && radius > kMaxPairRadius) consider(kTileWide16, 1);
-    if (box && radius <= kMaxPairRadius) {
-      consider(kTileWide32x2, 2);
-      consider(kTileWide16x2, 2);
-    }
-    // Gaussian window: tiles of one output band in 64-column strips run as two-band passes on 32
-    // or 16 columns where that costs less (the sums are the same, as always).
-    g.one_band[l] = kTileWide;
-    if (!box && radius <= kMaxPairRadius) {
-      double least = iter_cost(&s, 1, radius, kTileWide, 1, true);
-      for (int v : {kTileWide32x2, kTileWide16x2}) {
-        const double c = iter_cost(&s, 1, radius, v, 1, true);
-        if (c < least) {
-          least = c;
-          g.one_band[l] = v;
-        }
-      }
-      if (least < cost) {
-        g.variant[l] = kTileWide;
-        g.nb[l] = 1;
-      }
-    }
   }
   g.ein = (flags & OF_FLAG_INPUT_F32) ? Elem::F32 : Elem::U8;
   g.e0 = (flags & OF_FLAG_NORMALIZE) ? Elem::F32 : g.ein;
@@ -182,6 +73,16 @@ Geometry make_geometry(int H, int W, int levels, int radius, int iters, unsigned
   }
   g.bytes = off;
   return g;
+}
+
+// Tiles of a plan's iteration launches.
+void set_tiles(Geometry& g) {
+  for (int l = 0; l < g.L; ++l) {
+    const TileChoice c = choose_tiles(g.H[l], g.W[l], g.R, g.flags & OF_FLAG_GAUSSIAN_WINDOW);
+    g.variant[l] = c.variant;
+    g.nb[l] = c.nb;
+    g.one_band[l] = c.one_band;
+  }
 }
 
 Elem Geometry::elem(int l) const { return l == 0 ? e0 : ep; }
@@ -507,6 +408,7 @@ of_plan* of_plan_create_ex(int H, int W, int levels, int radius, int iters, unsi
                            void* workspace, size_t workspace_bytes) {
   if (!check_params(H, W, levels, radius, iters, flags)) return nullptr;
   Geometry g = make_geometry(H, W, levels, radius, iters, flags);
+  set_tiles(g);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) {
@@ -607,12 +509,13 @@ of_status of_compute_noalloc(int H, int W, int levels, int radius, int iters, un
   if (((uintptr_t)u | (uintptr_t)v) & 3) return set_error("u, v must be 4-byte aligned"), OF_EINVAL;
   if ((flags & OF_FLAG_INPUT_F32) && (((uintptr_t)I1 | (uintptr_t)I2) & 3))
     return set_error("float32 frames must be 4-byte aligned"), OF_EINVAL;
-  const Geometry g = make_geometry(H, W, levels, radius, iters, flags);
+  Geometry g = make_geometry(H, W, levels, radius, iters, flags);
   if (g.bytes > kNoallocScratchBytes)
     return set_error("of_compute_noalloc: this frame size needs " + std::to_string(g.bytes) +
                      " bytes of scratch, more than the library's " +
                      std::to_string(kNoallocScratchBytes)),
            OF_ENOMEM;
+  set_tiles(g);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   char* ws = nullptr;

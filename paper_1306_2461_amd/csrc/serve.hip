@@ -421,8 +421,8 @@ of_status of_server_push(of_server* s, of_session* const* ss, int n, const void*
   int level_bands[OF_MAX_LEVELS];
   for (int l = L - 1; l >= 0; --l) {
     std::vector<PlaneSize> sizes;
-    for (int i : flowing) sizes.push_back({ss[i]->g.H[l], ss[i]->g.W[l]});
-    level_bands[l] = best_bands(sizes.data(), (int)sizes.size(), R, kTileWide, kPushBands, kPushHeights);
+    for (int i : flowing) sizes.push_back({ss[i]->g.H[l], ss[i]->g.W[l], 1});
+    level_bands[l] = best_bands(sizes.data(), (int)sizes.size(), R, kPushBands, kPushHeights);
     const int TH = N * level_bands[l];
     std::vector<int4> off;   // all-masked tiles, after the active ones
     for (int q = 0; q < (int)flowing.size(); ++q) {
