@@ -80,3 +80,35 @@ def test_reach_of_a_pixel_that_is_not_finite(gpu_lib, r, levels, value):
                 torch.cuda.synchronize()
                 assert np.array_equal(_bits(us[0], vs[0]), ref), (fp16, bands, variant)
         b.close()
+
+
+@pytest.mark.parametrize("shape", [(40, 70), (1, 40), (40, 1), (2, 3)])
+@pytest.mark.parametrize("r", [0, 2, 8])
+def test_8_bit_frames_under_a_field_that_is_not_finite(gpu_lib, r, shape):
+    """One iteration from a caller's field that holds NaNs and infinities: 8-bit frames give what float
+    frames of the same values give, next to those pixels too (their samples come from the clamped
+    position, that of a NaN from the first pixel of its axis)."""
+    import torch
+    ofmi = gpu_lib
+    announce(f"8-bit frames, field not finite r={r} {shape}")
+    rng = np.random.default_rng(7)
+    H, W = shape
+    I = [to_dev(rng.integers(0, 256, size=shape).astype(np.uint8)) for _ in range(2)]
+    f = rng.uniform(-3, 3, size=(2, *shape)).astype(np.float32)
+    for k, value in enumerate([np.nan, np.inf, -np.inf, np.nan]):
+        f[k % 2, (5 + 9 * k) % H, (11 + 17 * k) % W] = value
+    f[:, H - 1, W - 1] = np.nan
+    got = []
+    for f32 in (False, True):
+        plan = ofmi.Plan(H, W, 1, r, 1, input_f32=f32, device=dev())
+        for variant in range(8) if r <= 8 else range(5):
+            plan.set_config({"bands": [1], "variant": [variant]})
+            un = torch.empty(shape, dtype=torch.float32, device=dev())
+            vn = torch.empty_like(un)
+            ofmi.debug_stage(plan, ofmi.OF_STAGE_ITERATE, 0,
+                             [i.float() if f32 else i for i in I] + [to_dev(f[0]), to_dev(f[1])], [un, vn])
+            torch.cuda.synchronize()
+            got.append(_bits(un, vn))
+        plan.close()
+    for g in got:
+        assert np.array_equal(g, got[-1])
