@@ -163,9 +163,6 @@ KernelTimer::~KernelTimer() {
   for (hipEvent_t e : pool) hipEventDestroy(e);
 }
 
-// Window taps and launch variant of one iteration (its mask set): the Gaussian-weighted window
-// (OF_FLAG_GAUSSIAN_WINDOW) fills the taps g(d) = exp(-d^2 / (2 sigma^2)), sigma = r/2,
-// d = -r..r, and marks the variant.
 void gaussian_taps(float* taps, int R) {
   for (int q = 0; q <= 2 * R; ++q) {
     const double d = q - R;
@@ -209,11 +206,18 @@ void band_cut(const uint8_t* m, int W, int c0, int c1, int y0, int e, int N, int
   th = ((r1 - 1 - ty0) / N + 1) * N;
 }
 
+// Tile variant that a level's launches run: with the Gaussian window wide tiles of one output band
+// take the form of least estimated cost (masked or not: a mask's flags are those of the same tiles).
+int launched_variant(const Geometry& g, int l) {
+  const bool one = (g.flags & OF_FLAG_GAUSSIAN_WINDOW) && g.nb[l] == 1 && g.variant[l] != kTileNarrow;
+  return one ? g.one_band[l] : g.variant[l];
+}
+
+// Launch variant of one iteration; the Gaussian window also fills the taps.
 int window_variant(const Geometry& g, int l, IterArgs& a) {
-  if (!(g.flags & OF_FLAG_GAUSSIAN_WINDOW)) return g.variant[l];
+  const int v = launched_variant(g, l);
+  if (!(g.flags & OF_FLAG_GAUSSIAN_WINDOW)) return v;
   gaussian_taps(a.taps, g.R);
-  // (a mask's flags are those of 64-column tiles)
-  const int v = g.variant[l] != kTileNarrow && g.nb[l] == 1 && !a.mask ? g.one_band[l] : g.variant[l];
   return v | kTileGauss;
 }
 
@@ -551,7 +555,7 @@ size_t tile_capacity(const Geometry& g, int l) {
 // uploaded to the plan's flag buffer (synchronous copy: outside graph capture only).
 hipError_t upload_tile_flags(of_plan* p, int l) {
   Geometry& g = p->g;
-  const int TW = tile_width(g.variant[l], g.R), TH = (2 * g.R + 1) * g.nb[l];
+  const int TW = tile_width(launched_variant(g, l), g.R), TH = (2 * g.R + 1) * g.nb[l];
   const std::vector<uint8_t> f = tile_flags(p->hmask[l].data(), g.H[l], g.W[l], TW, TH);
   g.tflags[l] = p->tflags + p->tf_off[l];
   return hipMemcpy(p->tflags + p->tf_off[l], f.data(), f.size(), hipMemcpyHostToDevice);
