@@ -83,9 +83,8 @@ typedef enum {
                                           kernels one by one) */
 
 /* Tile variants of the fused iteration kernel (launch configuration; results do not depend
- * on them).  NARROW: strips of 64 output columns, 5 threads per output column.  WIDE: the same
- * strips with about 12 threads per output column (two workgroups share a CU up to r = 8).
- * WIDE_LEAN: the same kernel as WIDE. */
+ * on them).  WIDE: strips of 64 output columns with about 12 threads per output column (two
+ * workgroups share a CU up to r = 8).  NARROW and WIDE_LEAN: the same kernel as WIDE. */
 #define OF_TILE_NARROW 0
 #define OF_TILE_WIDE 1
 #define OF_TILE_WIDE_LEAN 2
@@ -196,8 +195,9 @@ OF_API of_status of_plan_get_config(const of_plan* plan, int* bands, int* varian
 OF_API of_status of_plan_set_config(of_plan* plan, const int* bands, const int* variant);
 
 /* Autotuner: for each level in turn, times that level's iteration launches for bands in
- * {1,2,3,4,6,8,12,16} x the kernels the plan allows (six with the box window and r <= 8, four
- * with the box window above, two with the Gaussian window) on the given buffers (reps timed runs after one warm-up) and keeps the fastest.
+ * {1,2,3,4,6,8,12,16} x the kernels the plan allows (five with the box window and r <= 8, three
+ * with the box window above, one with the Gaussian window) on the given buffers (reps timed runs
+ * after one warm-up) and keeps the fastest.
  * Synchronises `stream`; writes u, v. */
 OF_API of_status of_plan_autotune(of_plan* plan, const void* I1, const void* I2, float* u,
                                   float* v, void* stream, int reps);
@@ -285,8 +285,8 @@ OF_API of_status of_batch_set_config(of_batch* b, const int* bands, const int* g
                                      const int* variant);
 
 /* Autotuner: for each level in turn, times that level's iteration launches for every
- * candidate (bands in {1,2,4,8,16,32}, grid in {one per tile, 256, 512, 1024, 2048}, NARROW and
- * WIDE tiles) on the given buffers (reps timed runs after one warm-up) and keeps the
+ * candidate (bands in {1,2,4,8,16,32}, grid in {one per tile, 256, 512, 1024, 2048}, WIDE
+ * tiles) on the given buffers (reps timed runs after one warm-up) and keeps the
  * fastest.  Synchronises `stream`.  The chosen configuration is read back with
  * of_batch_get_config. */
 OF_API of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* const* I2,

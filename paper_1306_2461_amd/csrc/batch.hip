@@ -722,7 +722,6 @@ of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* cons
   b->timer.mode = OF_TIMING_LAUNCH;
   static const int kBands[] = {1, 2, 4, 8, 16, 32};
   static const int kGrid[] = {0, 256, 512, 1024, 2048};
-  static const int kVariant[] = {kTileNarrow, kTileWide};
   hipError_t e = hipSuccess;
   // Coordinate descent, one level at a time: the iteration time of that level only.
   for (int l = 0; l < b->L && e == hipSuccess; ++l) {
@@ -732,9 +731,8 @@ of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* cons
     LevelCfg bestc = b->cfg[l];
     for (int nb : kBands) {
       if (nb > 1 && (2 * b->R + 1) * nb > 2 * maxH) continue;
-      for (int gr : kGrid)
-      for (int wd : kVariant) {
-        b->cfg[l] = {nb, gr, wd};
+      for (int gr : kGrid) {
+        b->cfg[l] = {nb, gr, kTileWide};
         e = upload_tiles(b);
         if (e != hipSuccess) break;
         double tl = 1e30;
@@ -765,7 +763,7 @@ of_status of_batch_autotune(of_batch* b, const void* const* I1, const void* cons
         }
         if (e == hipSuccess && tl < best) {
           best = tl;
-          bestc = {nb, gr, wd};
+          bestc = b->cfg[l];
         }
       }
     }

@@ -13,33 +13,31 @@ constexpr int kStripWidth = 64;
 // TW + 2R + 2 columns), so a thread's column, clamps and LDS offsets are formed once per tile, its
 // global offset is a per-thread constant added to a scalar row base, and P2 finds part of the
 // warped values and fields it needs in the thread's own registers.
-// Wide variants: the fewest rows per thread that a workgroup of at most 768 allows (three waves
-// per SIMD: two workgroups share a CU), rounded up to whole groups of four waves, one per SIMD:
-// e.g. r = 8 on 64-column strips samples 17 rows of 82 positions per band, two rows per thread at
-// 768 threads.  From r = 9 on 64-column strips would take three rows per thread, which spills at
-// the 80 registers of two workgroups per CU: one workgroup of up to 1024 there.  Narrow variants:
-// at least 5 threads per output column.
-template <int R, int TW, bool WIDE, int BB>
+// A workgroup takes the fewest rows per thread that 768 threads allow (three waves per SIMD: two
+// workgroups share a CU), rounded up to whole groups of four waves, one per SIMD: e.g. r = 8 on
+// 64-column strips samples 17 rows of 82 positions per band, two rows per thread at 768 threads.
+// From r = 9 on 64-column strips would take three rows per thread, which spills at the 80 registers
+// of two workgroups per CU: one workgroup of up to 1024 there.
+template <int R, int TW>
 constexpr bool two_groups() {
-  return WIDE && !(R > 8 && TW > 32);
+  return !(R > 8 && TW > 32);
 }
-template <int R, int TW, bool WIDE, int BB>
+template <int R, int TW, int BB>
 constexpr int group_threads() {
   const int N = 2 * R + 1, WC = TW + 2 * R + 2;
   const int rows = BB == 1 ? N : BB * N + 2;
-  if (!WIDE) return 5 * TW * BB;
   int k = 1;
-  while ((rows + k - 1) / k * WC > (two_groups<R, TW, WIDE, BB>() ? 768 : 1024)) ++k;
+  while ((rows + k - 1) / k * WC > (two_groups<R, TW>() ? 768 : 1024)) ++k;
   const int nt = ((rows + k - 1) / k * WC + 255) / 256 * 256;
   return nt < 5 * TW ? 5 * TW : nt;
 }
 
-template <int R, int TW_, bool WIDE = false, int BB = 1>
+template <int R, int TW_, int BB = 1>
 struct Cfg {
   static constexpr int N = 2 * R + 1;                 // band height = window height
   static constexpr int NR = BB * N;                   // product rows per pass (BB bands)
   static constexpr int TW = TW_;                      // output columns per strip
-  static constexpr int NT = group_threads<R, TW_, WIDE, BB>();   // threads per workgroup
+  static constexpr int NT = group_threads<R, TW_, BB>();   // threads per workgroup
   static constexpr int PC = TW + 2 * R;               // product columns
   static constexpr int WC = PC + 2;                   // warped-frame columns
   static constexpr int HL = 8 + 2 * R;                // products read per horizontal segment
@@ -60,7 +58,6 @@ struct Cfg {
   static constexpr int W2ROWS = P1_FIRST + G * K1;
   static constexpr int K3 = (5 * NR * NSEG + NT - 1) / NT;      // P3 items per thread
   static constexpr int RG = NT / TW;                            // P5 rows per round
-  static constexpr int K5 = (NR + RG - 1) / RG;                 // P5 rounds
   static_assert(NT >= WC && G * WC <= NT && NT % TW == 0 && 2 * WP <= NT,
                 "workgroup too small for the strip");
   // LDS: products [5][NR][PP], warped rows, window sums [5][NR][HP], and the field rows that P2
@@ -77,12 +74,12 @@ struct Cfg {
   static constexpr size_t HANDED_LDS_BYTES = LDS_BYTES + 2 * (size_t)RING * TW * sizeof(float);
 };
 
-// Wavefronts per SIMD the register allocation aims at: two workgroups of a wide variant share a
-// CU (one's barriers and load rounds hide behind the other's arithmetic), which leaves 80
-// registers per thread at three waves per SIMD each (from r = 11 the window rows of P4 need more).
-template <int R, int TW, bool WIDE, int BB>
+// Wavefronts per SIMD the register allocation aims at: two workgroups share a CU (one's barriers and
+// load rounds hide behind the other's arithmetic), which leaves 80 registers per thread at three
+// waves per SIMD each (from r = 11 the window rows of P4 need more).
+template <int R, int TW, int BB>
 constexpr int waves_per_simd() {
-  return two_groups<R, TW, WIDE, BB>() && R <= 10 ? 2 * ((Cfg<R, TW, WIDE, BB>::NT + 255) / 256) : 1;
+  return two_groups<R, TW>() && R <= 10 ? 2 * ((Cfg<R, TW, BB>::NT + 255) / 256) : 1;
 }
 
 }  // namespace ofmi

@@ -87,13 +87,12 @@ constexpr bool field_handed() {
 // registers at r = 8, which the launches from a coarser level otherwise spill), P4 forms only the rows
 // that are output and P5 is a single round: r = 8, iterations of a 512^2 level on 32 columns 8.4 -> 7.8 us,
 // of a 256^2 level on 16 columns 5.3 -> 5.1 us.
-template <typename T, int R, int TW, int MODE, bool WIDE, bool INTERIOR, bool GAUSS, int BB,
-          bool BUB, bool ONE>
+template <typename T, int R, int TW, int MODE, bool INTERIOR, bool GAUSS, int BB, bool BUB, bool ONE>
 __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands, int bx, int y0,
                                            bool pixel_mask, float4* sm4) {
   static_assert(!ONE || BB == 2, "one pass: both of its bands");
   const int nbands = ONE ? BB : bands;
-  using C = Cfg<R, TW, WIDE, BB>;
+  using C = Cfg<R, TW, BB>;
   constexpr int N = C::N, NR = C::NR, NT = C::NT, PC = C::PC, WC = C::WC, PP = C::PP, WP = C::WP,
                 HP = C::HP, K1 = C::K1, G = C::G, F0 = C::P1_FIRST;
   constexpr bool FLOW = MODE != kFlowZero;
@@ -592,8 +591,8 @@ __device__ __forceinline__ int xcd_order(int b, int nblocks) {
   return (b % kXcd) * per + b / kXcd;
 }
 
-template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, int BB, bool ONE>
-__global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd<R, TW, WIDE, BB>())) void lk_iter_strip(IterArgs a, int TH,
+template <typename T, int R, int TW, int MODE, bool GAUSS, int BB, bool ONE>
+__global__ __launch_bounds__((group_threads<R, TW, BB>()), (waves_per_simd<R, TW, BB>())) void lk_iter_strip(IterArgs a, int TH,
                                                                            int nbands, int tiles_x,
                                                                            int ntiles) {
   extern __shared__ float4 sm4[];
@@ -609,10 +608,10 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd
     }
     pixel_mask = f == 1;
   }
-  if (tile_interior<Cfg<R, TW, WIDE, BB>, MODE>(a, nbands, bx, y0))
-    strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
+  if (tile_interior<Cfg<R, TW, BB>, MODE>(a, nbands, bx, y0))
+    strip_tile<T, R, TW, MODE, true, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
   else
-    strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
+    strip_tile<T, R, TW, MODE, false, GAUSS, BB, true, ONE>(a, TH, nbands, bx, y0, pixel_mask, sm4);
 }
 
 // Batched form: workgroups stride over a work list of tiles of many pairs at the same
@@ -622,12 +621,12 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, BB>()), (waves_per_simd
 // without (2).
 // MASK: launches of batches with masks (the mask code costs the unmasked launches about 5 %
 // more instructions and is compiled out of them).
-template <typename T, int R, int TW, int MODE, bool WIDE, bool GAUSS, bool MASK>
-__global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>()), (waves_per_simd<R, TW, WIDE, 1>())) void lk_iter_batch(const IterArgs* __restrict__ args,
+template <typename T, int R, int TW, int MODE, bool GAUSS, bool MASK>
+__global__ __launch_bounds__((group_threads<R, TW, 1>()), (waves_per_simd<R, TW, 1>())) void lk_iter_batch(const IterArgs* __restrict__ args,
                                                                       const int4* __restrict__ tiles,
                                                                       int ntiles) {
   extern __shared__ float4 sm4[];
-  using C = Cfg<R, TW, WIDE>;
+  using C = Cfg<R, TW>;
   const int stride = (int)gridDim.x;
   for (int t = xcd_order(blockIdx.x, gridDim.x); t < ntiles; t += stride) {
     const int4 w = tiles[t];
@@ -645,19 +644,19 @@ __global__ __launch_bounds__((group_threads<R, TW, WIDE, 1>()), (waves_per_simd<
       }
     }
     if (tile_interior<C, MODE>(a, nb, w.y, w.z))
-      strip_tile<T, R, TW, MODE, WIDE, true, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
+      strip_tile<T, R, TW, MODE, true, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     else
-      strip_tile<T, R, TW, MODE, WIDE, false, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
+      strip_tile<T, R, TW, MODE, false, GAUSS, 1, false, false>(a, w.w, nb, w.y, w.z, pixel_mask, sm4);
     __syncthreads();
   }
 }
 
 // nb output bands per tile take nb + 1 bands (the first primes the vertical sums), rounded up
 // to whole passes of BB bands (a band past the tile's rows writes nothing).
-template <typename T, int R, int MODE, bool WIDE, bool GAUSS, int TWV = 0, int BB = 1, bool ONE = false>
+template <typename T, int R, int MODE, bool GAUSS, int TWV = 0, int BB = 1, bool ONE = false>
 hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   constexpr int TW = TWV ? TWV : kStripWidth;
-  using C = Cfg<R, TW, WIDE, BB>;
+  using C = Cfg<R, TW, BB>;
   constexpr size_t kLds = C::LDS_BYTES;
   static_assert(kLds <= 160 * 1024, "LDS footprint above 160 KB");
   const int TH = C::N * nb;
@@ -668,11 +667,11 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   if constexpr (kLds > 65536) {
     // Opt in to more than 64 KB of dynamic LDS (gfx950 has 160 KB per workgroup), once.
     static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB, ONE>),
+        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, GAUSS, BB, ONE>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (opt != hipSuccess) return opt;
   }
-  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, WIDE, GAUSS, BB, ONE>), dim3(grid),
+  hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, GAUSS, BB, ONE>), dim3(grid),
                      dim3(C::NT), kLds, s, a, TH, nbands, tx, ntiles);
   return hipGetLastError();
 }
@@ -680,25 +679,25 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
 template <typename T, int R, int MODE, bool GAUSS>
 hipError_t go_plain_g(const IterArgs& a, int nb, int variant, hipStream_t s) {
   switch (variant) {
-    case kTileNarrow: return go_plain_v<T, R, MODE, false, GAUSS>(a, nb, s);
+    case kTileNarrow:
     case kTileWide:
-    case kTileWideLean: return go_plain_v<T, R, MODE, true, GAUSS>(a, nb, s);
+    case kTileWideLean: return go_plain_v<T, R, MODE, GAUSS>(a, nb, s);
   }
   if constexpr (!GAUSS) {
     switch (variant) {   // narrow strips, one band per pass: box window only
-      case kTileWide32: return go_plain_v<T, R, MODE, true, false, 32>(a, nb, s);
-      case kTileWide16: return go_plain_v<T, R, MODE, true, false, 16>(a, nb, s);
+      case kTileWide32: return go_plain_v<T, R, MODE, false, 32>(a, nb, s);
+      case kTileWide16: return go_plain_v<T, R, MODE, false, 16>(a, nb, s);
     }
   }
   if constexpr (R <= kMaxPairRadius) {   // two bands per pass (Gaussian: tiles of one pass)
     const bool w32 = variant == kTileWide32x2 || variant == kTileLean32x2;
     if (w32 || variant == kTileWide16x2) {
       if (nb == 1)
-        return w32 ? go_plain_v<T, R, MODE, true, GAUSS, 32, 2, true>(a, nb, s)
-                   : go_plain_v<T, R, MODE, true, GAUSS, 16, 2, true>(a, nb, s);
+        return w32 ? go_plain_v<T, R, MODE, GAUSS, 32, 2, true>(a, nb, s)
+                   : go_plain_v<T, R, MODE, GAUSS, 16, 2, true>(a, nb, s);
       if constexpr (!GAUSS)
-        return w32 ? go_plain_v<T, R, MODE, true, false, 32, 2>(a, nb, s)
-                   : go_plain_v<T, R, MODE, true, false, 16, 2>(a, nb, s);
+        return w32 ? go_plain_v<T, R, MODE, false, 32, 2>(a, nb, s)
+                   : go_plain_v<T, R, MODE, false, 16, 2>(a, nb, s);
     }
   }
   return hipErrorInvalidValue;
@@ -711,43 +710,43 @@ hipError_t go_plain(const IterArgs& a, int nb, int variant, hipStream_t s) {
   return go_plain_g<T, R, MODE, false>(a, nb, variant, s);
 }
 
-template <typename T, int R, int MODE, bool WIDE, bool GAUSS, bool MASK>
+template <typename T, int R, int MODE, bool GAUSS, bool MASK>
 hipError_t go_batch_m(const BatchLaunch& b, hipStream_t s) {
   constexpr int TW = kStripWidth;
-  using C = Cfg<R, TW, WIDE>;
+  using C = Cfg<R, TW>;
   constexpr size_t kLds = field_handed<T, R, MODE, GAUSS, false>() ? C::HANDED_LDS_BYTES : C::LDS_BYTES;
   if constexpr (kLds > 65536) {
     static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>),
+        reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, GAUSS, MASK>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     if (opt != hipSuccess) return opt;
   }
   if (b.prime) {
     hipFuncAttributes attr;
     return hipFuncGetAttributes(
-        &attr, reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>));
+        &attr, reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, GAUSS, MASK>));
   }
-  hipLaunchKernelGGL((lk_iter_batch<T, R, TW, MODE, WIDE, GAUSS, MASK>), dim3(b.grid),
+  hipLaunchKernelGGL((lk_iter_batch<T, R, TW, MODE, GAUSS, MASK>), dim3(b.grid),
                      dim3(C::NT), kLds, s, b.args, b.tiles, b.ntiles);
   return hipGetLastError();
 }
 
-template <typename T, int R, int MODE, bool WIDE, bool GAUSS>
+template <typename T, int R, int MODE, bool GAUSS>
 hipError_t go_batch_v(const BatchLaunch& b, hipStream_t s) {
-  return b.masked ? go_batch_m<T, R, MODE, WIDE, GAUSS, true>(b, s)
-                  : go_batch_m<T, R, MODE, WIDE, GAUSS, false>(b, s);
+  return b.masked ? go_batch_m<T, R, MODE, GAUSS, true>(b, s)
+                  : go_batch_m<T, R, MODE, GAUSS, false>(b, s);
 }
 
 // b.variant: OF_TILE_NARROW, _WIDE or _WIDE_LEAN, plus kTileGauss for the Gaussian window.
 template <typename T, int R, int MODE>
 hipError_t go_batch(const BatchLaunch& b, hipStream_t s) {
   switch (b.variant) {
-    case kTileNarrow: return go_batch_v<T, R, MODE, false, false>(b, s);
+    case kTileNarrow:
     case kTileWide:
-    case kTileWideLean: return go_batch_v<T, R, MODE, true, false>(b, s);
-    case kTileNarrow | kTileGauss: return go_batch_v<T, R, MODE, false, true>(b, s);
+    case kTileWideLean: return go_batch_v<T, R, MODE, false>(b, s);
+    case kTileNarrow | kTileGauss:
     case kTileWide | kTileGauss:
-    case kTileWideLean | kTileGauss: return go_batch_v<T, R, MODE, true, true>(b, s);
+    case kTileWideLean | kTileGauss: return go_batch_v<T, R, MODE, true>(b, s);
   }
   return hipErrorInvalidValue;
 }

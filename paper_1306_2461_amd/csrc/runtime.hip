@@ -701,7 +701,7 @@ of_status of_plan_autotune(of_plan* p, const void* I1, const void* I2, float* u,
       if (nb > 1 && (2 * g.R + 1) * nb > 2 * g.H[l]) continue;
       for (int w = kTileNarrow; w < kTileVariants; ++w) {
         if (!tile_variant_valid(w, g.R, g.flags & OF_FLAG_GAUSSIAN_WINDOW)) continue;
-        if (w == kTileWideLean || w == kTileLean32x2) continue;   // the same kernels as wide, wide 32x2
+        if (w == kTileNarrow || w == kTileWideLean || w == kTileLean32x2) continue;   // wide, wide 32x2
         g.nb[l] = nb;
         g.variant[l] = w;
         if (g.mask[l]) e = upload_tile_flags(p, l);

@@ -11,11 +11,11 @@ namespace ofmi {
 
 namespace {
 
-template <int R, int TW, bool WIDE, int BB>
+template <int R, int TW, int BB>
 constexpr TileShape shape() {
-  using C = Cfg<R, TW, WIDE, BB>;
+  using C = Cfg<R, TW, BB>;
   // workgroups per CU: 24 waves of 80 registers where the kernel is compiled for two, 160 KB LDS
-  const int by_waves = waves_per_simd<R, TW, WIDE, BB>() > 1 ? 24 / ((C::NT + 63) / 64) : 1;
+  const int by_waves = waves_per_simd<R, TW, BB>() > 1 ? 24 / ((C::NT + 63) / 64) : 1;
   const int by_lds = (int)(160 * 1024 / C::LDS_BYTES);
   const int n = by_waves < by_lds ? by_waves : by_lds;
   return {TW, BB, C::NT, n < 1 ? 1 : n};
@@ -24,11 +24,11 @@ constexpr TileShape shape() {
 // Shapes of the variants of radius R (two bands per pass above kMaxPairRadius: none, wide).
 template <int R>
 constexpr std::array<TileShape, kTileVariants> shapes() {
-  constexpr TileShape wide = shape<R, kStripWidth, true, 1>();
+  constexpr TileShape wide = shape<R, kStripWidth, 1>();
   constexpr int P = R <= kMaxPairRadius ? R : 0;
-  constexpr TileShape w32 = R <= kMaxPairRadius ? shape<P, 32, true, 2>() : wide;
-  constexpr TileShape w16 = R <= kMaxPairRadius ? shape<P, 16, true, 2>() : wide;
-  return {shape<R, kStripWidth, false, 1>(), wide, wide, shape<R, 32, true, 1>(), shape<R, 16, true, 1>(),
+  constexpr TileShape w32 = R <= kMaxPairRadius ? shape<P, 32, 2>() : wide;
+  constexpr TileShape w16 = R <= kMaxPairRadius ? shape<P, 16, 2>() : wide;
+  return {wide, wide, wide, shape<R, 32, 1>(), shape<R, 16, 1>(),
           w32, w16, w32};
 }
 template <int... R>
