@@ -117,13 +117,16 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
   const Plane<float> UO(a.uout, H, W), VO(a.vout, H, W);
 
   // This thread's column of the warped frame and its first row of a pass (threads past the last
-  // group repeat that group: the same values to the same slots).
+  // group repeat that group: the same values to the same slots; where they are the most, at r = 0,
+  // they sample nothing: a pair of 1024^2 192 -> 140 us, 8 pairs of 640 x 480 at one band
+  // 514 -> 482 us).
   using DW = ConstDiv<WC, NT>;
   const int gq = (int)DW::q((unsigned)tid), lx = (int)DW::r((unsigned)tid, (unsigned)gq);
   const int gc = min(gq, G - 1), g = gc * K1;
   const int gx = INTERIOR ? x0 - R - 1 + lx : min(max(x0 - R - 1 + lx, 0), W - 1);
   const bool pcol_in = INTERIOR || (x0 - R - 1 + lx >= 0 && x0 - R - 1 + lx < W);
   const bool p2 = lx >= 1 && lx <= PC && gq < G;
+  const bool own = NT / WC < 2 * G || gq < G;
   constexpr int kLast = (G - 1) * K1;            // the last group's first row
   constexpr int kEnd = C::P1_ROWS - 1 - kLast;   // its last row
   // Image row i from image row ys (clamped).
@@ -267,7 +270,9 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
   constexpr bool AHEAD = MODE == kFlowSame;
   constexpr std::integral_constant<int, K1> kRows{};
   FieldRows<MODE, K1> f;
-  if constexpr (AHEAD) field(f, y0 - R - 1 + F0, g, kRows);
+  if constexpr (AHEAD) {
+    if (own) field(f, y0 - R - 1 + F0, g, kRows);
+  }
   for (int b = 0; b < nbands; b += BB) {
     const int tb = N * b;                        // first product row of the pass
     const int yw = y0 - R - 1 + tb;              // image row of LDS row 0
@@ -280,12 +285,17 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       const bool ext = BB == 1 && b == 0 && tid < 2 * WC;
       FieldRows<MODE, 1> ef;
       if (ext) field(ef, yw, gq, std::integral_constant<int, 1>{});
-      if constexpr (!AHEAD) field(f, yw + F0, g, kRows);
+      if constexpr (!AHEAD) {
+        if (own) field(f, yw + F0, g, kRows);
+      }
 #pragma unroll
-      for (int k = 0; k < K1; ++k) i1v[k] = frame1(yw, k);
+      for (int k = 0; k < K1; ++k) {
+        if (own) i1v[k] = frame1(yw, k);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
+        if (!own) continue;
         const float2 w = field_at(f, yw + F0, g, k);
         wu[k] = w.x;
         wv[k] = w.y;
@@ -299,9 +309,11 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
         es.issue(I2, H, W, gx, row_at(yw, gq), eu, ev);
       }
 #pragma unroll
-      for (int k = 0; k < K1; ++k) smp[k].issue(I2, H, W, gx, row_at(yw + F0 + k, g), wu[k], wv[k]);
+      for (int k = 0; k < K1; ++k) {
+        if (own) smp[k].issue(I2, H, W, gx, row_at(yw + F0 + k, g), wu[k], wv[k]);
+      }
       __builtin_amdgcn_sched_barrier(0);
-      keep_field(wu, wv, b == 0);
+      if (own) keep_field(wu, wv, b == 0);
       if (ext) {
         if (FLOW && gq == 1) {
           fcu[lx] = eu;
@@ -311,6 +323,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       }
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
+        if (!own) continue;
         wval[k] = smp[k].value();
         w2[(g + F0 + k) * WP + lx] = wval[k];
       }
@@ -318,7 +331,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
     __syncthreads();
     // ------------------------------------------------------------------ P2
     if constexpr (AHEAD) {
-      if (more) field(f, yw + NR + F0, g, kRows);
+      if (more && own) field(f, yw + NR + F0, g, kRows);
     }
     if constexpr (HANDED) {
       const int c = lx - R - 1;
