@@ -351,16 +351,16 @@ hipError_t launch_normalize(Elem t, const void* in1, const void* in2, float* out
   if (r < 0 || r > OF_MAX_NORMALIZE_RADIUS) return hipErrorInvalidValue;
   dim3 grid((W + NTW - 1) / NTW, (H + NTH - 1) / NTH, in2 ? 2 : 1);
   const size_t lds = normalize_lds_bytes(r);
-  // Up to 67.5 KB at the largest radius: opt in to more than 64 KB of dynamic LDS, once.
-  static const hipError_t opt32 = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&normalize_kernel<float>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)normalize_lds_bytes(OF_MAX_NORMALIZE_RADIUS));
   if (t == Elem::U8) {
     hipLaunchKernelGGL(r == OF_NORMALIZE_RADIUS ? normalize_u8_kernel<OF_NORMALIZE_RADIUS> : normalize_u8_kernel<-1>,
                        grid, dim3(256), normalize_u8_lds_bytes(r), s, (const uint8_t*)in1, (const uint8_t*)in2,
                        out1, out2, H, W, r, eps);
   } else if (t == Elem::F32) {
-    if (opt32 != hipSuccess) return opt32;
+    // up to 67.5 KB at the largest radius
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&normalize_kernel<float>),
+                                   normalize_lds_bytes(OF_MAX_NORMALIZE_RADIUS), done);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(normalize_kernel<float>, grid, dim3(256), lds, s, (const float*)in1, (const float*)in2, out1,
                        out2, H, W, r, eps);
   } else {

@@ -5,6 +5,7 @@
 #include <stddef.h>
 
 #include "common.h"
+#include "device_once.h"
 #include "tiles.h"
 
 namespace ofmi {
@@ -68,6 +69,17 @@ struct BatchLaunch {
   // ahead instead of paying on a request).
   bool prime = false;
 };
+
+// Lets `kernel` take `bytes` of dynamic LDS (more than 64 KB: gfx950 has 160 KB per workgroup) on the
+// current device; `done` belongs to the kernel.
+inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return once_per_device(done, dev, hipSuccess, [&] {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  });
+}
 
 // The iteration kernel's translation units: one per frame type and range of radii
 // [kRadiusGroups[g], kRadiusGroups[g+1]).

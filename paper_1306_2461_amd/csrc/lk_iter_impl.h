@@ -678,11 +678,10 @@ hipError_t go_plain_v(const IterArgs& a, int nb, hipStream_t s) {
   const int grid = (ntiles + 7) / 8 * 8;
   const int nbands = (nb + 1 + BB - 1) / BB * BB;
   if constexpr (kLds > 65536) {
-    // Opt in to more than 64 KB of dynamic LDS (gfx950 has 160 KB per workgroup), once.
-    static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, GAUSS, BB, ONE>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    if (opt != hipSuccess) return opt;
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e =
+        allow_lds(reinterpret_cast<const void*>(&lk_iter_strip<T, R, TW, MODE, GAUSS, BB, ONE>), kLds, done);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((lk_iter_strip<T, R, TW, MODE, GAUSS, BB, ONE>), dim3(grid),
                      dim3(C::NT), kLds, s, a, TH, nbands, tx, ntiles);
@@ -729,10 +728,10 @@ hipError_t go_batch_m(const BatchLaunch& b, hipStream_t s) {
   using C = Cfg<R, TW>;
   constexpr size_t kLds = field_handed<T, R, MODE, GAUSS, false>() ? C::HANDED_LDS_BYTES : C::LDS_BYTES;
   if constexpr (kLds > 65536) {
-    static const hipError_t opt = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, GAUSS, MASK>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    if (opt != hipSuccess) return opt;
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e =
+        allow_lds(reinterpret_cast<const void*>(&lk_iter_batch<T, R, TW, MODE, GAUSS, MASK>), kLds, done);
+    if (e != hipSuccess) return e;
   }
   if (b.prime) {
     hipFuncAttributes attr;
