@@ -208,30 +208,28 @@ struct Sample<uint8_t> {
 
 // Field of a launch's source at K successive rows of one column, in two steps (loads, then the
 // values).  The source is a compile-time parameter, so every kernel reads its field straight-line.
-template <int MODE, int K>
+// EVEN: the first row, before any clamp, is an even image row.
+template <int MODE, int K, bool EVEN = false>
 struct FieldRows {   // the previous iteration at the same level
   float u[K], v[K];
   template <bool INTERIOR>
-  __device__ __forceinline__ float2 at(int k, int, int, bool) const { return make_float2(u[k], v[k]); }
+  __device__ __forceinline__ float2 at(int k, int, int) const { return make_float2(u[k], v[k]); }
 };
 template <int K>
-struct FieldRows<kFlowZero, K> {
+struct FieldRows<kFlowZero, K, false> {
   template <bool INTERIOR>
-  __device__ __forceinline__ float2 at(int, int, int, bool) const { return make_float2(0.f, 0.f); }
+  __device__ __forceinline__ float2 at(int, int, int) const { return make_float2(0.f, 0.f); }
 };
 // The coarser level's Hc x Wc field: 2 * bilinear(coarse, x/2, y/2) at in-image pixel (x, y), base
 // floor(x/2), floor(y/2), fractions 0 or 1/2: every row reads its base row and the row after it, also
 // where the fraction is 0 (a field that is not finite there must not depend on how rows are dealt to
-// threads).  Two successive rows share two rows of the coarser level; an even second row lies one
-// further down and also takes the row after the pair's, which the next pair has loaded, or TAIL does
-// for the last pair of an even K.  (Without that row, an even second row's value being its base row
-// alone, a pair of 2048^2 took 236.0 instead of 238.7 us and 16 pairs of 1024^2 702.7 instead of 708.0,
-// but what a NaN or an infinity of a float frame reached followed from the tiles.  Its loads
-// under a branch on the parity: no faster.)
-template <int K>
-struct FieldRows<kFlowCoarse, K> {
+// threads).  A pair of rows from an even one on shares two rows of the coarser level.  Of a pair from
+// an odd row on, the second lies one further down and also takes the row after the pair's, which the
+// next pair has loaded, or TAIL does for the last pair of an even K.
+template <int K, bool EVEN>
+struct FieldRows<kFlowCoarse, K, EVEN> {
   static constexpr int NP = (K + 1) / 2;
-  static constexpr bool TAIL = K % 2 == 0;
+  static constexpr bool TAIL = K % 2 == 0 && !EVEN;
   float u00[NP], u01[NP], u10[NP], u11[NP], v00[NP], v01[NP], v10[NP], v11[NP], fa;
   float u20, u21, v20, v21;   // TAIL
   // Pair p, whose first row is y.  INTERIOR: the coarse row and column after every row's base exist.
@@ -263,17 +261,15 @@ struct FieldRows<kFlowCoarse, K> {
     }
   }
   __device__ __forceinline__ float across(float z0, float z1) const { return fmaf(fa, z1 - z0, z0); }
-  // Row k, at image row y; ya: the first row of its pair.  With even K the threads' first rows share
-  // one parity, y0_odd, which decides in tiles without clamps (INTERIOR).
+  // Row k, at image row y; ya: the first row of its pair.
   template <bool INTERIOR>
-  __device__ __forceinline__ float2 at(int k, int y, int ya, bool y0_odd) const {
-    constexpr bool UNI = INTERIOR && TAIL;
+  __device__ __forceinline__ float2 at(int k, int y, int ya) const {
     const int p = k / 2;
-    const float fb = (UNI ? y0_odd != (k % 2 == 1) : (y & 1) != 0) ? 0.5f : 0.f;
+    const float fb = (EVEN && INTERIOR ? k % 2 == 1 : (y & 1) != 0) ? 0.5f : 0.f;
     float tu = across(u00[p], u01[p]), tv = across(v00[p], v01[p]);
     float su = across(u10[p], u11[p]), sv = across(v10[p], v11[p]);
-    if (k % 2 == 1) {
-      const bool lower = UNI ? y0_odd : (y >> 1) != (ya >> 1);
+    if (!EVEN && k % 2 == 1) {
+      const bool lower = (y >> 1) != (ya >> 1);
       const int n = p + 1 < NP ? p + 1 : p;
       const float nu = p + 1 < NP ? across(u10[n], u11[n]) : across(u20, u21);
       const float nv = p + 1 < NP ? across(v10[n], v11[n]) : across(v20, v21);

@@ -28,19 +28,24 @@
 //   * two-bands-per-pass variants run the five phases once over two bands' rows, so a one-band
 //     tile (output band plus priming band) is one trip (Gaussian window: one-band tiles only).
 //
-// What bounds it: vector instructions and the waits between the five phases; HBM is at about
-// half of what a copy reaches.  Two workgroups per CU hide each other's barriers and load rounds,
-// which asks for at most 80 registers per thread (three waves per SIMD each) and no scratch: a
-// third of the vector instructions of an earlier form went into per-item index arithmetic, and
-// variants that kept more in flight (samples gathered a band ahead) spilled or fell to one
-// workgroup per CU and were slower.  Measured on level 0 of 16 pairs of 1024^2 (r = 8, uint8, tiles
+// What bounds it: vector instructions (two thirds of the CUs' clocks on a full device) and the waits
+// between the five phases; HBM is at about half of what a copy reaches.  Two workgroups per CU hide
+// each other's barriers and load rounds, which asks for at most 80 registers per thread (three waves
+// per SIMD each).  A third of the vector instructions of an earlier form went into per-item index
+// arithmetic, and variants that kept more in flight (samples gathered a band ahead) spilled or fell to
+// one workgroup per CU and were slower.  Measured on level 0 of 16 pairs of 1024^2 (r = 8, uint8, tiles
 // of 16 bands, iterations of a level averaged): 139.8 us per launch before the per-column mapping,
 // 8-bit samples and paired coarse rows below, 119.5 us with them, 113 us with the field handed on and
 // the first band's unused rows left out (16.8 Mpx: 2.7 TB/s of algorithmic bytes); a plan's 2048^2
-// level 0 (8 bands) 42.9 -> 31.7 us.  Vector memory instructions cost by
-// form, not by bytes: 64 lanes at unit stride 4.7 clocks per CU (bytes or dwords), 64-bit, stride-2
-// or unaligned 16-bit lanes 16 clocks, so every load and store here is one element per lane at unit
-// stride and a bilinear tap pair is two byte loads.
+// level 0 (8 bands) 42.9 -> 32 us.
+// Scratch: 32 bytes per thread in tiles of several two-band passes on 32 columns from a coarser level at
+// r = 8 (11 MiB written per launch of 1024^2; one launch of a level, at the sizes whose least estimate
+// they are), 8 and 12 in FP16 levels of 32-column strips at r = 9 and 10, 8 in Gaussian batches at r = 8
+// (8-bit frames; FP16 from a coarser level); the other forms have none.  At one workgroup per CU, which
+// would need none, Gaussian launches took 5 to 20 % longer.
+// Vector memory instructions cost by form, not by bytes: 64 lanes at unit stride 4.7 clocks per CU
+// (bytes or dwords), 64-bit, stride-2 or unaligned 16-bit lanes 16 clocks, so every load and store here
+// is one element per lane at unit stride and a bilinear tap pair is two byte loads.
 #pragma once
 
 #include <type_traits>
@@ -127,8 +132,15 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
   const bool pcol_in = INTERIOR || (x0 - R - 1 + lx >= 0 && x0 - R - 1 + lx < W);
   const bool p2 = lx >= 1 && lx <= PC && gq < G;
   const bool own = NT / WC < 2 * G || gq < G;
+  // EVEN: launches from a coarser level whose threads own pairs of rows start a pass one row early
+  // where its first row is odd (its last one the pass before: the same value to the same slot), so that
+  // every pair lies between the same two rows of the coarser level.  24 mixed pairs, first iteration of
+  // level 0: 316 us with a third row for every pair (and 8 to 40 bytes of scratch in 20 forms), 288 us so.
+  constexpr bool EVEN = MODE == kFlowCoarse && BB == 1 && K1 % 2 == 0;
+  static_assert(!EVEN || G * K1 > C::P1_ROWS, "no row to spare for a pass that starts early");
   constexpr int kLast = (G - 1) * K1;            // the last group's first row
-  constexpr int kEnd = C::P1_ROWS - 1 - kLast;   // its last row
+  // its last row (EVEN: of a pass that starts early, the only ones whose next pass asks for it)
+  constexpr int kEnd = C::P1_ROWS - 1 - kLast + (EVEN ? 1 : 0);
   // Image row i from image row ys (clamped).
   auto row_at = [&](int ys, int i) { return INTERIOR ? ys + i : min(max(ys + i, 0), H - 1); };
   // Element (gx, row i from image row ys) of a plane: interior tiles add a scalar row base to a
@@ -155,7 +167,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
     }
   };
   auto field_at = [&](const auto& f, int ys, int i, int k) {
-    return f.template at<INTERIOR>(k, row_at(ys + k, i), row_at(ys + k / 2 * 2, i), ys & 1);
+    return f.template at<INTERIOR>(k, row_at(ys + k, i), row_at(ys + k / 2 * 2, i));
   };
   // Frame 1 one row above this thread's k-th row of the pass whose LDS row 0 is image row yw.
   auto frame1 = [&](int yw, int k) {
@@ -229,7 +241,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
   const float* win = GAUSS ? pr : hs;
   constexpr int VP = GAUSS ? PP : HP;
   auto solve = [&](int tb, FieldRows<MODE, 1>* c) {
-    // slot of the pass's first output row, tile row tb - R + 1 (its sampled rows start at tb + 2)
+    // slot of the pass's first output row, tile row tb - 2R: R + 1 above its first sampled one
     const int s0 = wrap(ring_row + N);
 #pragma unroll
     for (int k = 0; k < K5; ++k) {
@@ -248,7 +260,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
           const int q = wrap(s0 + r) * TW + oc;
           f5 = make_float2(ru[q], rv[q]);
         } else {
-          f5 = c[k].template at<false>(0, gy, gy, false);
+          f5 = c[k].template at<false>(0, gy, gy);
         }
         solve_update(s[0], s[NR * VP], s[2 * NR * VP], s[3 * NR * VP], s[4 * NR * VP], f5.x, f5.y,
                      un, vn);
@@ -264,12 +276,12 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       }
     }
   };
-  // The field at a pass's warped-frame rows: a same-level launch loads it during P4 of the pass
+  // The field at a pass's warped-frame rows: a same-level launch loads it during P2 of the pass
   // before (ahead of that pass's stores, which a later load would be waited for with), a
-  // coarse-field launch, whose values take eight loads each, in P1.
+  // coarse-field launch, whose values take eight loads and more, in P1.
   constexpr bool AHEAD = MODE == kFlowSame;
   constexpr std::integral_constant<int, K1> kRows{};
-  FieldRows<MODE, K1> f;
+  FieldRows<MODE, K1, EVEN> f;
   if constexpr (AHEAD) {
     if (own) field(f, y0 - R - 1 + F0, g, kRows);
   }
@@ -277,6 +289,8 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
     const int tb = N * b;                        // first product row of the pass
     const int yw = y0 - R - 1 + tb;              // image row of LDS row 0
     const bool more = b + BB < nbands;
+    const int early = EVEN ? (yw + F0) & 1 : 0;  // rows that the threads' rows start above LDS row F0
+    const int ys = yw + F0 - early;              // image row of the first thread group's first row
     // ------------------------------------------------------------------ P1
     // Branch-free loads (clamped addresses).  In a tile's first band the two rows above it (LDS
     // rows 0 and 1) are sampled here too.
@@ -286,17 +300,17 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       FieldRows<MODE, 1> ef;
       if (ext) field(ef, yw, gq, std::integral_constant<int, 1>{});
       if constexpr (!AHEAD) {
-        if (own) field(f, yw + F0, g, kRows);
+        if (own) field(f, ys, g, kRows);
       }
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
-        if (own) i1v[k] = frame1(yw, k);
+        if (own) i1v[k] = frame1(yw - early, k);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
         if (!own) continue;
-        const float2 w = field_at(f, yw + F0, g, k);
+        const float2 w = field_at(f, ys, g, k);
         wu[k] = w.x;
         wv[k] = w.y;
       }
@@ -310,7 +324,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       }
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
-        if (own) smp[k].issue(I2, H, W, gx, row_at(yw + F0 + k, g), wu[k], wv[k]);
+        if (own) smp[k].issue(I2, H, W, gx, row_at(ys + k, g), wu[k], wv[k]);
       }
       __builtin_amdgcn_sched_barrier(0);
       if (own) keep_field(wu, wv, b == 0);
@@ -325,7 +339,7 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       for (int k = 0; k < K1; ++k) {
         if (!own) continue;
         wval[k] = smp[k].value();
-        w2[(g + F0 + k) * WP + lx] = wval[k];
+        w2[(g + F0 + k - early) * WP + lx] = wval[k];
       }
     }
     __syncthreads();
@@ -338,8 +352,9 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       if (c >= 0 && c < TW && gq < G) {
 #pragma unroll
         for (int k = 0; k < K1; ++k) {
-          if (kLast + k < N || g + k < N) {
-            const int q = wrap(ring_row + g + k) * TW + c;
+          const int i = g + k - early;
+          if ((kLast + k < N || i < N) && (!EVEN || k > 0 || i >= 0)) {
+            const int q = wrap(ring_row + i) * TW + c;
             ru[q] = wu[k];
             rv[q] = wv[k];
           }
@@ -350,9 +365,10 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
     // thread's own, the centre and the row above too from its second and third row on.
     if (p2) {
       constexpr int kSkip = 2 - F0;   // with two bands per pass rows -1 and 0 have no product above
-      const float* wr = w2 + (g + F0) * WP + lx;   // this thread's first warped row
+      const float* wr = w2 + (g + F0 - early) * WP + lx;   // this thread's first warped row
       const int up = kSkip == 0 || g > 0 ? 1 : 0;
-      float c1 = wr[-up * WP], c2 = wr[-2 * up * WP];   // one, two rows above
+      // one, two rows above (two above LDS row 1: any row, for the product that is left out below)
+      float c1 = wr[-up * WP], c2 = wr[-(EVEN && g < early ? 1 : 2) * up * WP];
       float fu = 0.f, fv = 0.f;       // field at the product position
       if constexpr (FLOW) {
         fu = fcu[gc * WP + lx];
@@ -360,8 +376,9 @@ __device__ __forceinline__ void strip_tile(const IterArgs& a, int TH, int bands,
       }
 #pragma unroll
       for (int k = 0; k < K1; ++k) {
-        if ((kSkip == 0 || g + k >= kSkip) && (kLast + k < C::P1_ROWS || g + k < C::P1_ROWS)) {
-          const int r = g + k - kSkip;
+        const int i = g + k - early;   // sampled row of the pass
+        if ((EVEN ? k > 0 || i >= 0 : kSkip == 0 || i >= kSkip) && (kLast + k < C::P1_ROWS || i < C::P1_ROWS)) {
+          const int r = i - kSkip;
           const float* row = wr + (k - 1) * WP;
           float ix = 0.5f * (row[1] - row[-1]);
           float iy = 0.5f * (wval[k] - c2);
