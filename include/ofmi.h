@@ -188,9 +188,10 @@ OF_API int of_levels_for_displacement(float dmax, int H, int W);
  * least estimated time for the level's size and radius among WIDE and, with the box window,
  * WIDE32 for r <= 3 and r > 8, WIDE16 for r > 8, WIDE32X2 and WIDE16X2 for r <= 8;
  * WIDE32, WIDE16 and the X2 variants are not available with OF_FLAG_GAUSSIAN_WINDOW, the X2
- * variants not above r = 8; with that flag WIDE and WIDE_LEAN tiles of one band run, up to r = 8,
- * as two bands per pass on 16 or 32 columns where that is estimated to take less time).  Arrays of `levels` entries.  set_config drops the plan's captured
- * graphs; OF_EINVAL for values out of range.  Results do not depend on the configuration. */
+ * variants not above r = 8; with that flag tiles of one band run, up to r = 8, as two bands per pass
+ * on 16 or 32 columns where that is estimated to take less time).  Arrays of `levels` entries.
+ * set_config drops the plan's captured graphs; OF_EINVAL for values out of range.  Results do not
+ * depend on the configuration. */
 OF_API of_status of_plan_get_config(const of_plan* plan, int* bands, int* variant);
 OF_API of_status of_plan_set_config(of_plan* plan, const int* bands, const int* variant);
 

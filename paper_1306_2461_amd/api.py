@@ -245,8 +245,8 @@ class Batch:
         return {"bands": list(bands), "grid": list(grid), "variant": list(variant)}
 
     def set_config(self, cfg):
-        """``cfg``: {"bands": [...], "grid": [...], "variant": [...] (optional; -1 = by tile
-        count, else one of OF_TILE_NARROW, OF_TILE_WIDE, OF_TILE_WIDE_LEAN)}, one entry per level."""
+        """``cfg``: {"bands": [...], "grid": [...], "variant": [...] (optional; -1 = the
+        default, else one of OF_TILE_NARROW, OF_TILE_WIDE, OF_TILE_WIDE_LEAN)}, one entry per level."""
         import ctypes
         bands = (ctypes.c_int * self.levels)(*cfg["bands"])
         grid = (ctypes.c_int * self.levels)(*cfg["grid"])

@@ -151,9 +151,9 @@ __device__ __forceinline__ int clamp_i(int x, int hi) {
   return r;
 }
 
-// I(x + u, y + v) by bilinear interpolation with clamped coordinates, in two steps, so that a thread issues the loads of all its
-// samples before it waits for the first: issue() forms the coordinates and starts the four
-// loads, value() interpolates.
+// I(x + u, y + v) by bilinear interpolation with clamped coordinates, in two steps, so that a thread
+// issues the loads of all its samples before it waits for the first: issue() forms the coordinates and
+// starts the four loads, value() interpolates.
 template <typename T>
 struct Sample {
   float z00, z01, z10, z11, a, b;

@@ -206,11 +206,10 @@ void band_cut(const uint8_t* m, int W, int c0, int c1, int y0, int e, int N, int
   th = ((r1 - 1 - ty0) / N + 1) * N;
 }
 
-// Tile variant that a level's launches run: with the Gaussian window wide tiles of one output band
+// Tile variant that a level's launches run: with the Gaussian window tiles of one output band
 // take the form of least estimated cost (masked or not: a mask's flags are those of the same tiles).
 int launched_variant(const Geometry& g, int l) {
-  const bool one = (g.flags & OF_FLAG_GAUSSIAN_WINDOW) && g.nb[l] == 1 && g.variant[l] != kTileNarrow;
-  return one ? g.one_band[l] : g.variant[l];
+  return (g.flags & OF_FLAG_GAUSSIAN_WINDOW) && g.nb[l] == 1 ? g.one_band[l] : g.variant[l];
 }
 
 // Launch variant of one iteration; the Gaussian window also fills the taps.
