@@ -30,15 +30,15 @@ METRIC = "frame pairs/s at 1024² (FP32 vs FP16-stored, % HBM peak); p50/p99 lat
 HBM_PEAK_GBS = 8000.0
 WORKLOAD = "c2"
 
-# Launch configurations the plan autotuner settles on for this workload (level 0: wide strips of
-# 4 bands, 64 or 32 columns): used by the --probe run, which profilers wrap, so that it needs
-# no autotuning launches.
-PROBE_CONFIGS = [{"bands": [4, 1, 1, 1], "variant": [1, 1, 6, 6]},
-                 {"bands": [4, 1, 1, 1], "variant": [3, 1, 6, 6]}]
+# Launch configurations of this workload's plan for the --probe run, which profilers wrap, so that it
+# needs no autotuning launches: the one that the autotuner settles on (level 0: 64-column strips of two
+# bands) and 32-column strips of four bands beside it.
+PROBE_CONFIGS = [{"bands": [2, 1, 1, 1], "variant": [1, 5, 6, 6]},
+                 {"bands": [4, 1, 1, 1], "variant": [3, 5, 6, 6]}]
 # The configuration the batch autotuner picked for 16 masked pairs of this workload (masked probe).
-MASK_PROBE_CONFIG = {"bands": [8, 4, 2, 1], "grid": [0, 2048, 2048, 2048], "variant": [2, 2, 2, 1]}
+MASK_PROBE_CONFIG = {"bands": [8, 4, 2, 1], "grid": [0, 0, 0, 1024], "variant": [1, 1, 1, 1]}
 # One of the configurations the batch autotuner picks for 16 pairs of this workload.
-PROBE_BATCH_CONFIG = {"bands": [16, 8, 2, 1], "grid": [2048, 512, 1024, 512], "variant": [2, 2, 2, 1]}
+PROBE_BATCH_CONFIG = {"bands": [16, 8, 2, 1], "grid": [0, 512, 512, 512], "variant": [1, 1, 1, 1]}
 # Sources of the fused iteration kernel: the HBM traffic recorded in the counter summary is
 # used only while they are unchanged.
 KERNEL_SOURCES = ["paper_1306_2461_amd/csrc/lk_iter_impl.h", "paper_1306_2461_amd/csrc/common.h",
