@@ -76,7 +76,7 @@ int main() {
     const double c = us_per_call([&](int i) { return choose_tiles(sizes[i & 3], sizes[i & 3], R, false); }, 4000);
     const double e = us_per_call([&](int i) { return exhaustive(sizes[i & 3], sizes[i & 3], R, false); }, 4000);
     std::printf("r=%d: %.3f us per level, exhaustive %.3f us\n", R, c, e);
-    if (c > e / 4) {
+    if (c > e / 2) {
       std::printf("slow choice\n");
       ++bad;
     }
